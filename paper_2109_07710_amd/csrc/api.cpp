@@ -61,10 +61,10 @@ int check_ws(const void* ws, size_t ws_bytes, size_t need)
     return CBW_OK;
 }
 
-DataParams data_params(const cbw_conv_desc* d, const void* dY, const void* wt, void* dX, int64_t npix,
+DataParamsStrided data_params(const cbw_conv_desc* d, const void* dY, const void* wt, void* dX, int64_t npix,
                        int groups)
 {
-    DataParams p{};
+    DataParamsStrided p{};
     p.dy = dY;
     p.wt = wt;
     p.dx = dX;
@@ -85,10 +85,10 @@ DataParams data_params(const cbw_conv_desc* d, const void* dY, const void* wt, v
 // Kernel parameters of the data gradient on NHWC tensors (dY, dX, x_mask
 // already in NHWC order), from a validated plan.
 void data_gemm_params(const cbw_conv_desc* desc, const DataPlan& plan, const void* dY, const void* wt,
-                      const uint32_t* x_mask, void* dX, void* ws, bool gather, bool no_split, DataParams* out,
+                      const uint32_t* x_mask, void* dX, void* ws, bool gather, bool no_split, DataParamsStrided* out,
                       CompactParams* cpo)
 {
-    DataParams p = data_params(desc, dY, wt, dX, plan.npix, plan.groups);
+    DataParamsStrided p = data_params(desc, dY, wt, dX, plan.npix, plan.groups);
     p.tile = plan.tile;
     p.mask = x_mask;
     p.ptiles = plan.ptiles;
@@ -96,6 +96,12 @@ void data_gemm_params(const cbw_conv_desc* desc, const DataPlan& plan, const voi
     p.nslots = kDataSlots;
     p.smax = no_split ? 1 : kDataMaxSplit;
     p.split = plan.split;   // gather mode: the split of its dense tiles, which it checks on the device
+    p.ncls = plan.ncls;
+    for (int c = 0; c < plan.ncls; ++c) {
+        const DataPlan::Class& k = plan.cls[c];
+        p.cls[c] = DataClass{k.tile0, (int)k.npix, k.nh, k.nw, k.i0, k.j0, k.a, k.b, k.nr, k.ns,
+                             make_fastdiv((uint32_t)k.nw), make_fastdiv((uint32_t)k.nh)};
+    }
     p.partial = plan.partial.bytes ? at<float>(ws, plan.partial) : nullptr;
     CompactParams cp{};
     if (gather) {
@@ -265,7 +271,7 @@ int run_bwd_data(const cbw_conv_desc* desc, const void* dY, const void* W, const
                                                !(flags & CBW_FLAG_NO_SKIP));
         if ((e = launch_bwd_data_pw(pp, plan.pw_grid, s, prof_events(0))) != hipSuccess) return hip_status(e);
     } else {
-        DataParams p;
+        DataParamsStrided p;
         CompactParams cp;
         data_gemm_params(desc, plan, dY, wt, x_mask, dX, ws, gather, no_split, &p, &cp);
         e = launch_data_prep(desc->dtype, W, wt, desc->K, desc->C, desc->R * desc->S, desc->w_layout == CBW_KRSC,
@@ -295,7 +301,7 @@ int run_fwd(const cbw_conv_desc* desc, const void* X, const void* W, void* Y, ui
 
     int* header = at<int>(ws, plan.header);
     void* wt = at<void>(ws, plan.wt);
-    DataParams p = data_params(&vd, X, wt, Y, plan.npix, plan.groups);
+    DataParamsStrided p = data_params(&vd, X, wt, Y, plan.npix, plan.groups);
     p.tile = plan.tile;
     p.ptiles = plan.ptiles;
     p.brows = plan.brows;
@@ -699,7 +705,7 @@ static int run_bwd_both(const cbw_conv_desc* desc, const void* X, const void* dY
                                 : (!masked ? MODE_DENSE : (gather ? MODE_GATHER : MODE_SELECT));
     int* header = at<int>(ws, dplan.header);
     void* wt = at<void>(ws, dplan.wt);
-    DataParams dp{};
+    DataParamsStrided dp{};
     CompactParams cp;
     if (tiled) data_gemm_params(desc, dplan, dY, wt, x_mask, dX, ws, gather, false, &dp, &cp);
     OccParams op{};

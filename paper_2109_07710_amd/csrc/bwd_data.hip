@@ -226,8 +226,45 @@ __device__ void gather_list(const DataParams& p, int G, int g, int row0, int row
     }
 }
 
+// Stride > 1, every pixel a row: the pixels (h, w) with equal residues
+// (h + pad_h) mod stride_h and (w + pad_w) mod stride_w form a class, and only
+// the filter taps of the same residues reach them, each at the dY pixel
+// (i - r', j - s') for the class coordinates i = (h + pad_h) / stride_h and
+// the tap r = a + stride_h r'.  The tiles cover one class each and walk its
+// taps alone: a class is a unit-stride problem, and no step multiplies zeros
+// (walking all R * S taps of every pixel runs stride_h * stride_w times the
+// products that land).  3x3 stride 2, N = 32, masked: 128 -> 256 channels at
+// 56x56 62 -> 35 us, 256 -> 512 168 -> 71 us, 64 -> 128 at 112x112 125 -> 56 us; 1x1
+// stride 2, where three classes of four have no tap, 24.3 -> 23 us.
+
+// The class a pixel tile of the dense tiling belongs to.
+__device__ __forceinline__ int tile_class(const DataParamsStrided& p, int ptile)
+{
+    int c = 0;
+    while (c + 1 < p.ncls && ptile >= p.cls[c + 1].tile0) ++c;
+    return c;
+}
+// Image and class coordinates (n, i, j) of row x of class c.
+__device__ __forceinline__ void class_coords(const DataClass& c, int x, int& n, int& i, int& j)
+{
+    const uint32_t nh = fdiv((uint32_t)x, c.div_w);
+    j = x - (int)nh * c.nw + c.j0;
+    n = (int)fdiv(nh, c.div_h);
+    i = (int)nh - n * c.nh + c.i0;
+}
+// Pixel of dX at row x of class c.
+__device__ __forceinline__ int class_pixel(const DataParamsStrided& p, const DataClass& c, int x)
+{
+    int n, i, j;
+    class_coords(c, x, n, i, j);
+    return (n * p.H + i * p.stride_h + c.a - p.pad_h) * p.W + j * p.stride_w + c.b - p.pad_w;
+}
+
+template <bool UNIT>
+using ParamsFor = std::conditional_t<UNIT, DataParams, DataParamsStrided>;
+
 template <typename T, int MODE, bool UNIT, int TI>
-__global__ __launch_bounds__(Tile<TI>::NT) void bwd_data_kernel(DataParams p)
+__global__ __launch_bounds__(Tile<TI>::NT) void bwd_data_kernel(ParamsFor<UNIT> p)
 {
     using TL = Tile<TI>;
     constexpr int BM = TL::BM, BN = TL::BN, WN = TL::WN, NW = TL::NW;
@@ -288,7 +325,7 @@ __global__ __launch_bounds__(Tile<TI>::NT) void bwd_data_kernel(DataParams p)
     // once; when the preparation launch flagged a dead pixel, the copies are
     // dropped and the tiles are rebuilt over the live lists.
     const int kchunks = (p.K + (CH * Elem<T>::E) - 1) / (CH * Elem<T>::E);
-    const int nsteps = p.R * p.S * kchunks;
+    const int nsteps = p.R * p.S * kchunks;   // (of the largest class, when classes are used: an upper bound)
     constexpr int GG = MODE == MODE_GATHER ? kGatherMaxGroups : 1;
     __shared__ int gsum_s[GG * NW];
     __shared__ int gtot_s[GG];
@@ -307,8 +344,14 @@ __global__ __launch_bounds__(Tile<TI>::NT) void bwd_data_kernel(DataParams p)
     int nsplit = 1, brows = 0, item = 0, z = 0, ctile = 0, ptile = 0, c0 = 0, row0 = 0;
     int fnw = 0, wrow0 = 0, nrows = 0, st_begin = 0, nloc = 0;
     bool active = false, listed = false;
+    // the class of the item's pixels (stride > 1, not listed) and its taps
+    bool classed = false;
+    int cls = 0, taps_r = p.R, taps_s = p.S;
     uint32_t a_off[IA];   // A: byte offset without the step part, kOOB when no such channel
-    int a_lc[IA];
+    // logical chunk of the lane in every row group it copies: swz8 of row
+    // 8 (wave + NW j) + lane / 8 does not depend on j (NW is even)
+    static_assert(NW % 2 == 0, "one logical chunk per lane");
+    const int c_lc = pch ^ swz8(8 * wave + lrow8);
     auto map_item = [&](bool dense_rule) {
         int ntiles;
         if (dense_rule) {
@@ -332,7 +375,10 @@ __global__ __launch_bounds__(Tile<TI>::NT) void bwd_data_kernel(DataParams p)
         const int nitems = ntiles * nsplit;
         active = (int)blockIdx.x < nitems;   // uniform across the workgroup
         if (!active) return;
-        item = xcd_remap(blockIdx.x, nitems);
+        // classes differ in steps and come longest first: taken in dispatch
+        // order, so that every XCD gets its share of each
+        if constexpr (!UNIT) classed = dense_rule && p.ncls > 0;
+        item = classed ? (int)blockIdx.x : xcd_remap(blockIdx.x, nitems);
         const int tile = item / nsplit;
         z = item - tile * nsplit;
         if (dense_rule) {
@@ -354,15 +400,26 @@ __global__ __launch_bounds__(Tile<TI>::NT) void bwd_data_kernel(DataParams p)
         wrow0 = 16 * (wn * fn_base + (wn < fn_rem ? wn : fn_rem));
         nrows = dense_rule ? p.npix : __builtin_amdgcn_readfirstlane(gtot_s[ctile]);
         listed = !dense_rule && nrows < p.npix;
-        st_begin = (int)((int64_t)z * nsteps / nsplit);
-        nloc = (int)((int64_t)(z + 1) * nsteps / nsplit) - st_begin;
+        int steps = nsteps;
+        taps_r = p.R;
+        taps_s = p.S;
+        if constexpr (!UNIT) {
+            if (classed) {
+                cls = tile_class(p, ptile);
+                row0 = (ptile - p.cls[cls].tile0) * brows;
+                nrows = p.cls[cls].npix;
+                taps_r = p.cls[cls].nr;
+                taps_s = p.cls[cls].ns;
+                steps = taps_r * taps_s * kchunks;
+            }
+        }
+        st_begin = (int)((int64_t)z * steps / nsplit);
+        nloc = (int)((int64_t)(z + 1) * steps / nsplit) - st_begin;
 #pragma unroll
         for (int j = 0; j < IA; ++j) {
             const int row = 8 * (wave + NW * j) + lrow8;
-            const int lc = pch ^ swz8(row);
             const int c = c0 + row;
-            a_lc[j] = lc;
-            a_off[j] = (row < BM && c < p.C) ? (uint32_t)(c * p.K + lc * E) * ESZ : kOOB;
+            a_off[j] = (row < BM && c < p.C) ? (uint32_t)(c * p.K + c_lc * E) * ESZ : kOOB;
         }
     };
 
@@ -370,30 +427,49 @@ __global__ __launch_bounds__(Tile<TI>::NT) void bwd_data_kernel(DataParams p)
     // (filters) does not depend on the pixel list, so step 0's is issued
     // before the list is read.
     auto load_a = [&](int buf, int tap, int k0) {
-        const uint32_t a_step = (uint32_t)((tap * p.C) * p.K + k0) * ESZ;
+        int ft = tap;   // the filter tap
+        if constexpr (!UNIT) {
+            if (classed) {
+                const int r = tap / taps_s, s = tap - r * taps_s;
+                ft = (p.cls[cls].a + r * p.stride_h) * p.S + p.cls[cls].b + s * p.stride_w;
+            }
+        }
+        const uint32_t a_step = (uint32_t)((ft * p.C) * p.K + k0) * ESZ;
 #pragma unroll
         for (int j = 0; j < IA; ++j) {
             const int g = wave + NW * j;
             if (IA * NW * 8 == BM || g * 8 < BM) {
-                const bool kin = kfull || (k0 + a_lc[j] * E < p.K);
+                const bool kin = kfull || (k0 + c_lc * E < p.K);
                 buf_load16_lds(rs_wt, kin ? a_off[j] + a_step : kOOB,
                                lds_addr(&As[buf][(wave_u + NW * j) * 8 * CH]));
             }
         }
     };
 
-    int bn_[IB], bh_[IB], bw_[IB], bbase[IB], b_lc[IB];
+    // the lane's rows: coordinates (kNoRow: no pixel, every tap misses) and
+    // element offset of dY at them -- of their image, where taps are walked
+    // with strides (every tap of every pixel, stride > 1)
+    constexpr int kNoRow = -(1 << 30);
+    int bh_[IB], bw_[IB], bbase[IB];
     uint32_t b_off[IB];   // B byte offset for the current tap, kOOB when the tap misses
     int ld_tap = 0, ld_kc = 0;  // next step to load
 
     auto set_tap = [&](int tap) {
-        const int r = tap / p.S, s = tap - r * p.S;
-        if (UNIT) {
+        const int r = tap / taps_s, s = tap - r * taps_s;
+        if (!UNIT && classed) {
+            const int delta = -(r * p.Q + s) * p.K;
+#pragma unroll
+            for (int j = 0; j < IB; ++j) {
+                const int hh = bh_[j] - r, ww = bw_[j] - s;
+                const bool ok = (unsigned)hh < (unsigned)p.P && (unsigned)ww < (unsigned)p.Q;
+                b_off[j] = ok ? (uint32_t)(bbase[j] + delta) * ESZ : kOOB;
+            }
+        } else if (UNIT) {
             const int delta = ((p.pad_h - r) * p.Q + (p.pad_w - s)) * p.K;
 #pragma unroll
             for (int j = 0; j < IB; ++j) {
                 const int hh = bh_[j] + p.pad_h - r, ww = bw_[j] + p.pad_w - s;
-                const bool ok = bn_[j] >= 0 && hh >= 0 && hh < p.P && ww >= 0 && ww < p.Q;
+                const bool ok = (unsigned)hh < (unsigned)p.P && (unsigned)ww < (unsigned)p.Q;
                 b_off[j] = ok ? (uint32_t)(bbase[j] + delta) * ESZ : kOOB;
             }
         } else {
@@ -401,11 +477,11 @@ __global__ __launch_bounds__(Tile<TI>::NT) void bwd_data_kernel(DataParams p)
             for (int j = 0; j < IB; ++j) {
                 b_off[j] = kOOB;
                 const int hh = bh_[j] + p.pad_h - r, ww = bw_[j] + p.pad_w - s;
-                if (bn_[j] < 0 || hh < 0 || ww < 0) continue;
+                if (hh < 0 || ww < 0) continue;
                 if (hh % p.stride_h || ww % p.stride_w) continue;
                 const int pp = hh / p.stride_h, qq = ww / p.stride_w;
                 if (pp >= p.P || qq >= p.Q) continue;
-                b_off[j] = (uint32_t)(((bn_[j] * p.P + pp) * p.Q + qq) * p.K + b_lc[j] * E) * ESZ;
+                b_off[j] = (uint32_t)(bbase[j] + (pp * p.Q + qq) * p.K) * ESZ;
             }
         }
     };
@@ -416,7 +492,7 @@ __global__ __launch_bounds__(Tile<TI>::NT) void bwd_data_kernel(DataParams p)
         for (int j = 0; j < IB; ++j) {
             const int g = wave_u + NW * j;
             if (g * 8 < brows) {
-                const bool kin = kfull || (k0 + b_lc[j] * E < p.K);
+                const bool kin = kfull || (k0 + c_lc * E < p.K);
                 buf_load16_lds(rs_dy, kin ? b_off[j] + b_step : kOOB,
                                lds_addr(&Bs[buf][(wave_u + NW * j) * 8 * CH]));
             }
@@ -509,10 +585,14 @@ __global__ __launch_bounds__(Tile<TI>::NT) void bwd_data_kernel(DataParams p)
     auto start_item = [&]() {
         ld_tap = st_begin / kchunks;
         ld_kc = st_begin % kchunks;
-        load_a(0, ld_tap, ld_kc * BK);
+        if (UNIT || nloc > 0) load_a(0, ld_tap, ld_kc * BK);
         for (int i = tid; i < BN; i += NT) {
             const int r = row0 + i;
-            pix_s[i] = (!listed && i < brows && r < nrows) ? r : -1;
+            int pix = (!listed && i < brows && r < nrows) ? r : -1;
+            if constexpr (!UNIT) {
+                if (classed && pix >= 0) pix = class_pixel(p, p.cls[cls], r);
+            }
+            pix_s[i] = pix;
         }
         if (listed) gather_list<NT>(p, BM, ctile, row0, min(row0 + brows, nrows), pix_s, gscr_s);
         __syncthreads();
@@ -524,23 +604,26 @@ __global__ __launch_bounds__(Tile<TI>::NT) void bwd_data_kernel(DataParams p)
 #pragma unroll
         for (int j = 0; j < IB; ++j) {
             const int row = 8 * (wave + NW * j) + lrow8;
-            const int lc = pch ^ swz8(row);
-            b_lc[j] = lc;
             const int pix = row < BN ? pix_s[row] : -1;
-            bn_[j] = -1; bh_[j] = 0; bw_[j] = 0;
+            bh_[j] = kNoRow; bw_[j] = 0; bbase[j] = 0;
             if (pix >= 0) {
+                int n;
                 const uint32_t nh = fdiv((uint32_t)pix, p.div_w);
                 bw_[j] = pix - (int)nh * p.W;
-                const uint32_t n = fdiv(nh, p.div_h);
-                bh_[j] = (int)nh - (int)n * p.H;
-                bn_[j] = (int)n;
+                n = (int)fdiv(nh, p.div_h);
+                bh_[j] = (int)nh - n * p.H;
+                if constexpr (!UNIT) {
+                    if (classed) class_coords(p.cls[cls], row0 + row, n, bh_[j], bw_[j]);
+                }
+                const bool at_pixel = UNIT || classed;
+                bbase[j] = ((n * p.P + (at_pixel ? bh_[j] : 0)) * p.Q + (at_pixel ? bw_[j] : 0)) * p.K + c_lc * E;
             }
-            // unit stride: element offset of dY at (n, h, w) before the tap shift
-            bbase[j] = ((bn_[j] * p.P + bh_[j]) * p.Q + bw_[j]) * p.K + lc * E;
         }
-        set_tap(ld_tap);
-        load_b(0, ld_kc * BK);
-        if (++ld_kc == kchunks) { ld_kc = 0; ++ld_tap; }
+        if (UNIT || nloc > 0) {   // (a class may have no tap: its pixels are zero)
+            set_tap(ld_tap);
+            load_b(0, ld_kc * BK);
+            if (++ld_kc == kchunks) { ld_kc = 0; ++ld_tap; }
+        }
         mask_lds = SEL && (p.C % 32) == 0 && nsplit == 1;
         if (mask_lds) fetch_mask();
     };
@@ -588,7 +671,11 @@ __global__ __launch_bounds__(Tile<TI>::NT) void bwd_data_kernel(DataParams p)
             if (blockIdx.x == 0) p.counts[tid] = tot;
         }
         __syncthreads();
-        map_item(false);
+        // (a stale flag with every pixel live keeps the dense tiling, which the
+        // split reduction takes for it)
+        bool all = true;
+        for (int g = 0; g < p.ctiles; ++g) all &= gtot_s[g] == p.npix;
+        map_item(__builtin_amdgcn_readfirstlane((int)all) != 0);
         if (active) start_item();
         wait_vmem();
         __syncthreads();
@@ -917,8 +1004,8 @@ __global__ __launch_bounds__(256) void fwd_prep_kernel(const T* __restrict__ w, 
 // fixed grid; exits at once when the GEMM did not split.
 constexpr int kMaxDataSplit = 16;   // the planner's kDataMaxSplit (checked at dispatch)
 
-template <typename T, int MODE, int TI>
-__device__ __forceinline__ void data_reduce_block(const DataParams& p, int block, int nblocks)
+template <typename T, int MODE, int TI, bool UNIT>
+__device__ __forceinline__ void data_reduce_block(const ParamsFor<UNIT>& p, int block, int nblocks)
 {
     constexpr int BM = Tile<TI>::BM, BN = Tile<TI>::BN;
     constexpr int E = Elem<T>::E;
@@ -935,7 +1022,8 @@ __device__ __forceinline__ void data_reduce_block(const DataParams& p, int block
             ntiles += (p.counts[g] + BN - 1) / BN;
             all &= p.counts[g] == p.npix;
         }
-        nsplit = data_split(ntiles, nsteps, p.nslots, p.smax);
+        if (all) ntiles = p.ptiles * p.ctiles;   // the dense tiling
+        nsplit = all ? p.split : data_split(ntiles, nsteps, p.nslots, p.smax);
         dense_map = all;
     } else {
         ntiles = p.ptiles * p.ctiles;
@@ -957,12 +1045,25 @@ __device__ __forceinline__ void data_reduce_block(const DataParams& p, int block
             ptile = tile / p.ctiles;
             ctile = tile - ptile * p.ctiles;
         }
-        const int r = ptile * BN + pr;
-        const int nrows = dense_map ? p.npix : p.counts[ctile];
         const int c = ctile * BM + cl;
-        if (r >= nrows || c >= p.C) continue;
-        // (a fully live group's list is 0, 1, 2, ... and is not stored)
-        const int pix = nrows < p.npix ? p.lists[(int64_t)ctile * p.npix + r] : r;
+        int pix;
+        bool classed = false;
+        if constexpr (!UNIT) {
+            classed = dense_map && p.ncls > 0;
+            if (classed) {
+                const DataClass& k = p.cls[tile_class(p, ptile)];
+                const int r = (ptile - k.tile0) * BN + pr;
+                if (r >= k.npix || c >= p.C) continue;
+                pix = class_pixel(p, k, r);
+            }
+        }
+        if (UNIT || !classed) {
+            const int r = ptile * BN + pr;
+            const int nrows = dense_map ? p.npix : p.counts[ctile];
+            if (r >= nrows || c >= p.C) continue;
+            // (a fully live group's list is 0, 1, 2, ... and is not stored)
+            pix = nrows < p.npix ? p.lists[(int64_t)ctile * p.npix + r] : r;
+        }
         const int64_t o = (int64_t)pix * p.C + c;
         // the footprint word goes out with the partials, not after their sum
         // (a second round trip per vector otherwise)
@@ -1018,10 +1119,10 @@ __device__ __forceinline__ void data_reduce_block(const DataParams& p, int block
     }
 }
 
-template <typename T, int MODE, int TI>
-__global__ __launch_bounds__(256) void splitk_data_reduce_kernel(DataParams p)
+template <typename T, int MODE, int TI, bool UNIT>
+__global__ __launch_bounds__(256) void splitk_data_reduce_kernel(ParamsFor<UNIT> p)
 {
-    data_reduce_block<T, MODE, TI>(p, blockIdx.x, gridDim.x);
+    data_reduce_block<T, MODE, TI, UNIT>(p, blockIdx.x, gridDim.x);
 }
 
 // Workgroups of the data gradient's split reduction: one output vector per
@@ -1046,8 +1147,8 @@ int data_reduce_blocks(const DataParams& p)
 // partials (G threads per output), the next dx_blocks blocks the data
 // gradient's split tiles (when its reduction was split; they exit at once
 // otherwise).
-template <typename T>
-__global__ __launch_bounds__(256) void bwd_reduce_kernel(DataParams dp, int dx_mode, int dx_blocks, ReduceParams rp)
+template <typename T, bool UNIT>
+__global__ __launch_bounds__(256) void bwd_reduce_kernel(ParamsFor<UNIT> dp, int dx_mode, int dx_blocks, ReduceParams rp)
 {
     const int b = blockIdx.x;
     if (b < rp.blocks) {
@@ -1062,17 +1163,17 @@ __global__ __launch_bounds__(256) void bwd_reduce_kernel(DataParams dp, int dx_m
     }
     const int db = b - rp.blocks;
     if (dx_mode == MODE_GATHER) {
-        if (dp.tile == 0) data_reduce_block<T, MODE_GATHER, 0>(dp, db, dx_blocks);
-        else if (dp.tile == 1) data_reduce_block<T, MODE_GATHER, 1>(dp, db, dx_blocks);
-        else data_reduce_block<T, MODE_GATHER, 2>(dp, db, dx_blocks);
+        if (dp.tile == 0) data_reduce_block<T, MODE_GATHER, 0, UNIT>(dp, db, dx_blocks);
+        else if (dp.tile == 1) data_reduce_block<T, MODE_GATHER, 1, UNIT>(dp, db, dx_blocks);
+        else data_reduce_block<T, MODE_GATHER, 2, UNIT>(dp, db, dx_blocks);
     } else if (dx_mode == MODE_SELECT) {
-        if (dp.tile == 0) data_reduce_block<T, MODE_SELECT, 0>(dp, db, dx_blocks);
-        else if (dp.tile == 1) data_reduce_block<T, MODE_SELECT, 1>(dp, db, dx_blocks);
-        else data_reduce_block<T, MODE_SELECT, 2>(dp, db, dx_blocks);
+        if (dp.tile == 0) data_reduce_block<T, MODE_SELECT, 0, UNIT>(dp, db, dx_blocks);
+        else if (dp.tile == 1) data_reduce_block<T, MODE_SELECT, 1, UNIT>(dp, db, dx_blocks);
+        else data_reduce_block<T, MODE_SELECT, 2, UNIT>(dp, db, dx_blocks);
     } else {
-        if (dp.tile == 0) data_reduce_block<T, MODE_DENSE, 0>(dp, db, dx_blocks);
-        else if (dp.tile == 1) data_reduce_block<T, MODE_DENSE, 1>(dp, db, dx_blocks);
-        else data_reduce_block<T, MODE_DENSE, 2>(dp, db, dx_blocks);
+        if (dp.tile == 0) data_reduce_block<T, MODE_DENSE, 0, UNIT>(dp, db, dx_blocks);
+        else if (dp.tile == 1) data_reduce_block<T, MODE_DENSE, 1, UNIT>(dp, db, dx_blocks);
+        else data_reduce_block<T, MODE_DENSE, 2, UNIT>(dp, db, dx_blocks);
     }
 }
 
@@ -1116,15 +1217,18 @@ hipError_t launch_data_prep(int dtype, const void* w, void* wt, int K, int C, in
     return hipGetLastError();
 }
 
-hipError_t launch_bwd_reduce(int dtype, int dx_mode, const DataParams& dp, bool dx_reduce, const ReduceParams& rp,
+hipError_t launch_bwd_reduce(int dtype, int dx_mode, const DataParamsStrided& dp, bool dx_reduce, const ReduceParams& rp,
                              hipStream_t stream)
 {
     const int dx_blocks = dx_reduce ? data_reduce_blocks(dp) : 0;
     const int nb = rp.blocks + dx_blocks;
     if (nb == 0) return hipSuccess;
     if (dx_reduce && (dp.tile < 0 || dp.tile >= kDataTileCount || dp.smax > kMaxDataSplit)) return hipErrorInvalidValue;
-    if (dtype == 1) bwd_reduce_kernel<uint16_t><<<nb, 256, 0, stream>>>(dp, dx_mode, dx_blocks, rp);
-    else bwd_reduce_kernel<float><<<nb, 256, 0, stream>>>(dp, dx_mode, dx_blocks, rp);
+    const bool unit = dp.ncls == 0;
+    if (dtype == 1 && unit) bwd_reduce_kernel<uint16_t, true><<<nb, 256, 0, stream>>>(dp, dx_mode, dx_blocks, rp);
+    else if (dtype == 1) bwd_reduce_kernel<uint16_t, false><<<nb, 256, 0, stream>>>(dp, dx_mode, dx_blocks, rp);
+    else if (unit) bwd_reduce_kernel<float, true><<<nb, 256, 0, stream>>>(dp, dx_mode, dx_blocks, rp);
+    else bwd_reduce_kernel<float, false><<<nb, 256, 0, stream>>>(dp, dx_mode, dx_blocks, rp);
     return hipGetLastError();
 }
 
@@ -1149,26 +1253,30 @@ namespace {
 
 // GEMM (and, when the reduction may be split, the partial-tile reduction) of
 // one element type, mode and tile shape.
-template <typename T, int MODE, int TI>
-hipError_t launch_shape(const DataParams& p, int nb, hipStream_t stream, const ProfEvents& ev, bool with_reduce)
+template <typename T, int MODE, int TI, bool UNIT>
+hipError_t launch_strides(const ParamsFor<UNIT>& p, int nb, hipStream_t stream, const ProfEvents& ev, bool with_reduce)
 {
-    hipError_t e_launch;
-    if (p.stride_h == 1 && p.stride_w == 1)
-        e_launch = launch_timed(bwd_data_kernel<T, MODE, true, TI>, dim3(nb), dim3(Tile<TI>::NT), stream, ev, p);
-    else
-        e_launch = launch_timed(bwd_data_kernel<T, MODE, false, TI>, dim3(nb), dim3(Tile<TI>::NT), stream, ev, p);
-    hipError_t e = e_launch;
+    hipError_t e =
+        launch_timed(bwd_data_kernel<T, MODE, UNIT, TI>, dim3(nb), dim3(Tile<TI>::NT), stream, ev, p);
     if (e != hipSuccess) return e;
     // in gather mode the split is only known on the device
     if (with_reduce && (MODE == MODE_GATHER || p.split > 1)) {
-        splitk_data_reduce_kernel<T, MODE, TI><<<data_reduce_blocks(p), 256, 0, stream>>>(p);
+        splitk_data_reduce_kernel<T, MODE, TI, UNIT><<<data_reduce_blocks(p), 256, 0, stream>>>(p);
         e = hipGetLastError();
     }
     return e;
 }
 
+template <typename T, int MODE, int TI>
+hipError_t launch_shape(const DataParamsStrided& p, int nb, hipStream_t stream, const ProfEvents& ev, bool wr)
+{
+    if (p.stride_h == 1 && p.stride_w == 1) return launch_strides<T, MODE, TI, true>(p, nb, stream, ev, wr);
+    if constexpr (MODE == MODE_FWD) return hipErrorInvalidValue;   // the forward runs stride 1 only
+    else return launch_strides<T, MODE, TI, false>(p, nb, stream, ev, wr);
+}
+
 template <typename T, int MODE>
-hipError_t launch_mode(const DataParams& p, int nb, hipStream_t stream, const ProfEvents& ev, bool wr)
+hipError_t launch_mode(const DataParamsStrided& p, int nb, hipStream_t stream, const ProfEvents& ev, bool wr)
 {
     if (p.tile == 0) return launch_shape<T, MODE, 0>(p, nb, stream, ev, wr);
     if (p.tile == 1) return launch_shape<T, MODE, 1>(p, nb, stream, ev, wr);
@@ -1176,7 +1284,7 @@ hipError_t launch_mode(const DataParams& p, int nb, hipStream_t stream, const Pr
 }
 
 template <typename T>
-hipError_t launch_type(int mode, const DataParams& p, int nb, hipStream_t stream, const ProfEvents& ev, bool wr)
+hipError_t launch_type(int mode, const DataParamsStrided& p, int nb, hipStream_t stream, const ProfEvents& ev, bool wr)
 {
     if (mode == MODE_DENSE) return launch_mode<T, MODE_DENSE>(p, nb, stream, ev, wr);
     if (mode == MODE_SELECT) return launch_mode<T, MODE_SELECT>(p, nb, stream, ev, wr);
@@ -1186,7 +1294,7 @@ hipError_t launch_type(int mode, const DataParams& p, int nb, hipStream_t stream
 
 }  // namespace
 
-hipError_t launch_bwd_data(int dtype, int mode, const DataParams& p, hipStream_t stream, const ProfEvents& ev,
+hipError_t launch_bwd_data(int dtype, int mode, const DataParamsStrided& p, hipStream_t stream, const ProfEvents& ev,
                            bool with_reduce)
 {
     // enough workgroups for every tile of the dense tiling unsplit, or for
@@ -1199,7 +1307,7 @@ hipError_t launch_bwd_data(int dtype, int mode, const DataParams& p, hipStream_t
     if (p.tile < 0 || p.tile >= kDataTileCount || p.smax > kMaxDataSplit) return hipErrorInvalidValue;
     // the weight gradient's reduction in tail workgroups, four 256-thread
     // blocks each
-    DataParams q = p;
+    DataParamsStrided q = p;
     q.gemm_grid = nb;
     int tail = 0;
     if (q.dw_red.blocks > 0) {

@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "common.hpp"
+#include "tiles.hpp"
 
 namespace cbw {
 
@@ -48,6 +49,16 @@ struct ReduceParams {
     int blocks;              // 256-thread workgroups of the weight-gradient part
 };
 
+// A pixel class of the strided data gradient: rows h = stride_h i + a - pad_h
+// for the class coordinates i0 <= i < i0 + nh, columns likewise, and the
+// filter taps r = a + stride_h r' for r' < nr, s likewise.
+struct DataClass {
+    int tile0;               // first pixel tile (the classes' tiles follow one another)
+    int npix;                // N * nh * nw
+    int nh, nw, i0, j0, a, b, nr, ns;
+    FastDiv div_w, div_h;    // class row index -> (n, i - i0, j - j0)
+};
+
 struct DataParams {
     const void* dy;          // [N*P*Q][K]
     const void* wt;          // [R*S][C][K]
@@ -81,6 +92,13 @@ struct DataParams {
     // 256-thread blocks, after every GEMM workgroup has been dispatched.
     ReduceParams dw_red;
     int gemm_grid;
+};
+// The same with the pixel classes, for strides above 1 (a type of its own:
+// carrying a kilobyte of classes through every launch cost the unit-stride
+// split reduction 3 us).
+struct DataParamsStrided : DataParams {
+    int ncls;                // 0: every tap of every pixel
+    DataClass cls[kDataMaxClasses];   // most taps first
 };
 
 // Row-window data gradient (3 x 3, stride 1, C = K = 64, bf16, NHWC): a
@@ -206,12 +224,12 @@ int compact_block_pixels();
 hipError_t launch_data_prep(int dtype, const void* w, void* wt, int K, int C, int RS, int krsc, int* header,
                             int mode, const CompactParams* cp, hipStream_t stream, const OccParams* op = nullptr);
 // with_reduce = false leaves a split reduction to launch_bwd_reduce.
-hipError_t launch_bwd_data(int dtype, int mode, const DataParams& p, hipStream_t stream, const ProfEvents& ev,
+hipError_t launch_bwd_data(int dtype, int mode, const DataParamsStrided& p, hipStream_t stream, const ProfEvents& ev,
                            bool with_reduce = true);
 // The weight gradient's split-K reduction (rp.blocks workgroups, none when
 // dW was written directly) and, when dx_reduce, the data gradient's split
 // tiles, in one launch.
-hipError_t launch_bwd_reduce(int dtype, int dx_mode, const DataParams& dp, bool dx_reduce, const ReduceParams& rp,
+hipError_t launch_bwd_reduce(int dtype, int dx_mode, const DataParamsStrided& dp, bool dx_reduce, const ReduceParams& rp,
                              hipStream_t stream);
 // Forward preparation: Wf[tap'][k][c] = W[k][tap][c] with tap' the flipped tap
 // (R-1-r, S-1-s), the workspace header stamped, and `zero_words` words of

@@ -1,4 +1,6 @@
 // Host-only validation and workspace planning (see plan.hpp).
+#include <algorithm>
+
 #include "plan.hpp"
 
 namespace cbw {
@@ -51,6 +53,36 @@ int require_nhwc(const cbw_conv_desc* d)
     const int st = validate_desc(d);
     if (st != CBW_OK) return st;
     return d->act_layout == CBW_NHWC ? CBW_OK : CBW_ERR_UNSUPPORTED;
+}
+
+// The pixel classes of a strided data gradient, most taps first (ties keep
+// the residue order); empty classes (no such row or column) are left out.
+static int data_classes(const cbw_conv_desc* d, DataPlan::Class* out)
+{
+    if ((d->stride_h == 1 && d->stride_w == 1) || (int64_t)d->stride_h * d->stride_w > kDataMaxClasses) return 0;
+    auto axis = [](int size, int pad, int st, int filt, int a, int* first, int* n, int* taps) {
+        // positions h = st * i + a - pad in [0, size)
+        *first = pad > a ? (pad - a + st - 1) / st : 0;
+        const int last = size - 1 + pad - a;   // st * i <= last
+        *n = last >= 0 ? std::max(0, last / st - *first + 1) : 0;
+        *taps = a < filt ? (filt - 1 - a) / st + 1 : 0;
+    };
+    int n = 0;
+    for (int a = 0; a < d->stride_h; ++a)
+        for (int b = 0; b < d->stride_w; ++b) {
+            DataPlan::Class c;
+            c.a = a;
+            c.b = b;
+            axis(d->H, d->pad_h, d->stride_h, d->R, a, &c.i0, &c.nh, &c.nr);
+            axis(d->W, d->pad_w, d->stride_w, d->S, b, &c.j0, &c.nw, &c.ns);
+            if (c.nh == 0 || c.nw == 0) continue;
+            c.npix = (int64_t)d->N * c.nh * c.nw;
+            out[n++] = c;
+        }
+    std::stable_sort(out, out + n, [](const DataPlan::Class& x, const DataPlan::Class& y) {
+        return x.nr * x.ns > y.nr * y.ns;
+    });
+    return n;
 }
 
 int data_tile_index(int C)
@@ -165,6 +197,19 @@ int plan_data(const cbw_conv_desc* d, bool masked, DataPlan* out, bool no_split,
     }
     p.brows = data_rows_pick(cand, p.bn, kDataSlots);
     p.ptiles = (int)((p.npix + p.brows - 1) / p.brows);
+    p.ncls = data_classes(d, p.cls);
+    if (p.ncls > 0) {
+        // full tiles: a tile's time hardly depends on its rows, and with
+        // classes of different taps rounds of tiles say little (128 -> 256
+        // channels, 56 x 56, N = 32: 35 us with 448 rows, 37 with 416, 39
+        // with 224; 256 -> 512: 71, 79, 93)
+        p.brows = p.bn;
+        p.ptiles = 0;
+        for (int c = 0; c < p.ncls; ++c) {
+            p.cls[c].tile0 = p.ptiles;
+            p.ptiles += (int)((p.cls[c].npix + p.brows - 1) / p.brows);
+        }
+    }
     const int bk = 8 * (d->dtype == CBW_BF16 ? 8 : 4);
     p.nsteps = d->R * d->S * ((d->K + bk - 1) / bk);
     p.split = no_split ? 1 : host_data_split(p.ptiles * p.groups, p.nsteps);

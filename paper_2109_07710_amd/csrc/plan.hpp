@@ -35,6 +35,13 @@ struct DataPlan {
     int ptiles = 0, nsteps = 0;
     int brows = 0;          // dense / select: pixel rows per tile (data_rows_pick)
     int split = 1;          // dense / select: host-chosen reduction split
+    // stride > 1: pixel classes (see DataClass), most taps first; 0 when the
+    // strides have more than kDataMaxClasses residues
+    int ncls = 0;
+    struct Class {
+        int a = 0, b = 0, i0 = 0, j0 = 0, nh = 0, nw = 0, nr = 0, ns = 0, tile0 = 0;
+        int64_t npix = 0;
+    } cls[kDataMaxClasses];
     // Row-window kernel (data_rows_eligible): a workgroup per (column
     // segment, strip of rows_per_strip output rows), nbw 16-column blocks
     // per wave at most; it replaces the tiled GEMM and its compaction.

@@ -33,6 +33,9 @@ struct DataTile {
     int bm, bn, wm, wn;
 };
 constexpr int kDataTileCount = 3;
+// Pixel classes (stride_h * stride_w of them) the strided data gradient
+// separates; larger strides walk every tap of every pixel.
+constexpr int kDataMaxClasses = 16;
 // Compaction groups (channel tiles) the gather mode handles; wider layers
 // run the masked data gradient without compaction (footprint select only).
 constexpr int kGatherMaxGroups = 16;

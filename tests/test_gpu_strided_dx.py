@@ -1,0 +1,76 @@
+"""GPU parity of the strided data gradient's pixel classes against the fp64
+oracle: strides equal and unequal per axis, classes without a tap (1x1,
+stride 2), without a pixel (one row or column), more residues than classes are
+kept for (5 x 5: every tap of every pixel), pads past the filter, filters
+smaller than the stride; tilings split and not; every pixel live (the class tiling) and whole pixels dead (the
+live lists).
+"""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2109_07710_amd as cb
+from parity import check_values, tol_for
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # N, C, H, W, K, R, S, stride, pad, dtype
+    (2, 64, 13, 11, 40, 3, 3, (2, 2), (1, 1), "bf16"),      # few tiles: split reduction
+    (3, 72, 9, 10, 136, 1, 1, (2, 2), (0, 0), "bf16"),      # three classes of four have no tap
+    (1, 128, 1, 37, 64, 1, 3, (2, 3), (0, 1), "bf16"),      # one row: classes without a pixel
+    (2, 256, 12, 15, 64, 5, 4, (3, 1), (4, 0), "bf16"),     # nine taps at most, stride 1 along one axis
+    (2, 32, 17, 9, 32, 2, 2, (4, 4), (1, 3), "bf16"),       # filter smaller than the stride, pad past the filter
+    (2, 64, 16, 16, 24, 3, 3, (5, 5), (1, 1), "bf16"),      # 25 residues: every tap of every pixel
+    (5, 128, 130, 94, 16, 3, 3, (2, 2), (1, 1), "bf16"),    # 144 tiles of 448 rows
+    (9, 256, 96, 80, 8, 3, 3, (2, 2), (1, 1), "bf16"),      # 312 tiles of 224 rows
+    (3, 64, 224, 200, 8, 3, 3, (2, 2), (1, 1), "bf16"),     # 264 tiles of 512 rows
+    (2, 36, 21, 18, 20, 3, 3, (2, 2), (1, 1), "f32"),
+    (4, 128, 120, 118, 12, 3, 3, (2, 2), (1, 1), "f32"),    # 128 full tiles: split in two
+]
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    cb.lib()
+
+
+@pytest.mark.parametrize("dead", [False, True], ids=["live", "dead_pixels"])
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "%s_N%dC%dK%d_%dx%d_f%dx%d_s%dx%d" % (
+    c[9], c[0], c[1], c[4], c[2], c[3], c[5], c[6], *c[7]))
+def test_strided_dx(case, dead):
+    N, C, H, W, K, R, S, st, pd, dt = case
+    print("\n[case] strided dX %s dead=%s" % (case, dead), flush=True)
+    rng = np.random.default_rng([210907710, 91, N, C, H, W, K])
+    td = torch.bfloat16 if dt == "bf16" else torch.float32
+    desc = cb.ConvDesc.make(N, C, H, W, K, R, S, st, pd, dtype=dt)
+    x = np.maximum(rng.standard_normal((N, H, W, C), dtype=np.float32), 0.0)
+    if dead:
+        x[rng.random((N, H, W)) < 0.5] = 0.0
+    else:
+        x[..., 0] += 0.5
+    x = torch.from_numpy(x).to(td)
+    w = torch.from_numpy(rng.standard_normal((K, R, S, C), dtype=np.float32)).to(td)
+    dy = torch.from_numpy(rng.standard_normal((N, desc.P, desc.Q, K), dtype=np.float32)).to(td)
+    dx = {k: torch.full((N, H, W, C), float("nan"), dtype=td, device="cuda") for k in ("dense", "select", "masked")}
+    xm = torch.zeros(cb.cbw_mask_words(desc), dtype=torch.int32, device="cuda")
+    cb.cbw_relu_mask_pack(desc, x.cuda(), xm)
+    ws = cb.workspace(desc, cb.CBW_OP_BWD_DATA_MASKED)
+    cb.conv_bwd_data(desc, dy.cuda(), w.cuda(), dx["dense"], ws)
+    cb.conv_bwd_data_masked(desc, dy.cuda(), w.cuda(), xm, dx["select"], ws, cb.CBW_FLAG_NO_SKIP)
+    cb.conv_bwd_data_masked(desc, dy.cuda(), w.cuda(), xm, dx["masked"], ws)
+    torch.cuda.synchronize()
+    dy64 = oracle.nhwc_to_nchw(dy.double().numpy())
+    w64 = oracle.krsc_to_kcrs(w.double().numpy())
+    ref, ab, nt = oracle.conv_bwd_data(dy64, w64, (H, W), st, pd, with_bound=True)
+    mask = oracle.relu_mask(oracle.nhwc_to_nchw(x.double().numpy()))
+    for k, g in dx.items():
+        m = 1 if k == "dense" else mask
+        out = oracle.nhwc_to_nchw(g.float().cpu().double().numpy())
+        check_values(out, ref * m, ab * m, nt * m, tol_for(dt), dt == "bf16", "strided dX, " + k)
+        if k != "dense":   # killed outputs are the +0.0 bit pattern
+            bits = g.view(torch.int16 if dt == "bf16" else torch.int32).cpu().numpy()
+            assert not (oracle.nchw_to_nhwc(~mask) & (bits != 0)).any()
