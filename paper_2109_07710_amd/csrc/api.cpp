@@ -582,6 +582,8 @@ static WeightParams weight_gemm_params(const cbw_conv_desc* desc, const WeightPl
     p.bk = plan.bk;
     p.tpg = plan.tpg;
     p.tgroups = plan.tgroups;
+    p.subc = plan.subc;
+    p.subk = plan.subk;
     p.cg = plan.cg;
     p.rows = plan.rows ? 1 : 0;
     p.mode_flags = (int)flags;

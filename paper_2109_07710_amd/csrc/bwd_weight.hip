@@ -5,11 +5,9 @@
 // (weight-gradient phase, Sec. IV-B).  GEMM view: M = channels c of one tap
 // (A = shifted X), N = output channels k (B = dY), reduction = pixels.  Both
 // operands are pixel-major in NHWC, so the reduction index is the strided
-// one.  Each staging thread loads an E x E block (E pixels x E channels, one
-// 16-byte vector per pixel, coalesced along channels), transposes it in
-// registers and writes E vectors of E consecutive pixels into LDS, where the
-// MFMA fragments then read reduction-contiguous 16-byte chunks.  Half of the
-// workgroup stages X blocks, the other half dY blocks.
+// one: bf16 fragments are transposed on their way out of LDS, and the fp32
+// matrix instructions take one reduction index per lane group, so there a
+// pixel's row is a fragment as it lies in memory.
 //
 // Input sparsity (Sec. III-B): a (pixel chunk, k tile) block in which dY is
 // entirely zero contributes exactly zero, so the workgroup skips its loads
@@ -30,12 +28,7 @@ namespace {
 
 constexpr int BM = CBW_DW_BM;   // channels c per tile
 constexpr int BN = CBW_DW_BN;   // output channels k per tile
-constexpr int WM = CBW_DW_WM, WN = CBW_DW_WN;
-constexpr int NT = 64 * WM * WN;
-constexpr int HT = NT / 2;      // staging threads per operand
-constexpr int TM = BM / WM, TN = BN / WN;
-constexpr int FM = TM / 16, FN = TN / 16;
-constexpr int CH = 8;           // 16-byte chunks per LDS row (128 bytes)
+constexpr int F32_BK = 32;      // pixels per fp32 chunk
 constexpr int OCC_WIN = 1024;   // occupancy bytes cached per workgroup
 
 // The chunk range [begin, end) of split z of a weight-gradient tile, with the
@@ -231,67 +224,45 @@ __device__ __forceinline__ int next_live_chunk(const WeightParams& p, const uint
     }
     return end;
 }
-static_assert(BM == BN, "both operands share the staging layout");
+// fp32.  v_mfma_f32_16x16x4_f32 takes, per lane, one element of A and one of
+// B at reduction index lane / 16: with four pixels as the reduction, a lane
+// that loads the 16 bytes of pixel lane / 16 at columns 4 (lane % 16) .. +3
+// holds four fragments as they lie in memory, fragment j covering columns
+// 4 i + j, i = 0..15.  Two such loads (X at the tap, dY) feed the 16 matrix
+// instructions of a 64 x 64 tile, 512 cycles of the matrix unit for 2 KB, so
+// the operands go straight from global memory (the L1 and L2 serve the waves
+// that share them) into a register ring one chunk ahead: no LDS, no barrier.
+//
+// A workgroup's four waves (one per SIMD) share one 64 x 64 (c, k) part of a
+// (tap, channel tile, k tile) and its split's chunk range, each taking every
+// fourth chunk; their sums are added through LDS in a fixed order, so few
+// partials reach global memory.  Three workgroups fit a CU (registers), so
+// that one starts or finishes under the others' matrix work (256 -> 256
+// channels, 28 x 28, N = 8: 85 us, against 94 with eight waves alone on a
+// CU; 78 with the offsets advanced instead of decoded at every load).  Bound by the matrix unit where the pixels
+// are many (256 FLOP per clock and CU).  The 256 x 256 tiles this replaces
+// padded narrower layers to 256 columns twice, transposed both operands
+// through registers and ran their steps as a serial chain.  The call with its
+// occupancy and reduction launches: 128 -> 128 channels, 28 x 28, N = 16
+// 139 -> 45 us (a 23 us floor at 157 TFLOP/s); 64 -> 64 at 112 x 112, N = 4
+// 482 -> 45; 8 -> 64 likewise 480 -> 43; 16 -> 16 at 16 x 16, N = 2 44 -> 13.
+constexpr int F32_NW = 4;
+constexpr int F32_T = 64;               // columns and output channels per workgroup
+constexpr int F32_RROW = F32_T + 4;     // floats per row of the reduction buffer (padded)
 
-// Chunk swizzle: bijective on 16 consecutive rows (fragment reads) and
-// two-to-one on rows 8c + j, c = 0..15 (transposed block writes).
-__device__ __forceinline__ int swz(int row) { return ((row >> 1) ^ (row >> 3)) & 7; }
-
-template <typename T>
-__device__ __forceinline__ void transpose_block(const uint4 (&v)[Elem<T>::E], uint4 (&u)[Elem<T>::E]);
-
-// 8 x 8 bf16: v[e] holds channels 0..7 of pixel e; u[j] gets pixels 0..7 of
-// channel j.
-template <>
-__device__ __forceinline__ void transpose_block<uint16_t>(const uint4 (&v)[8], uint4 (&u)[8])
+__global__ __launch_bounds__(F32_NW * 64, 3) void bwd_weight_f32_kernel(WeightParams p)
 {
-    uint32_t d[8][4], o[8][4];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) { d[e][0] = v[e].x; d[e][1] = v[e].y; d[e][2] = v[e].z; d[e][3] = v[e].w; }
-#pragma unroll
-    for (int m = 0; m < 4; ++m)           // channel pair (2m, 2m+1)
-#pragma unroll
-        for (int mp = 0; mp < 4; ++mp) {  // pixel pair (2mp, 2mp+1)
-            const uint32_t a = d[2 * mp][m], b = d[2 * mp + 1][m];
-            o[2 * m][mp] = (a & 0xffffu) | (b << 16);
-            o[2 * m + 1][mp] = (a >> 16) | (b & 0xffff0000u);
-        }
-#pragma unroll
-    for (int j = 0; j < 8; ++j) u[j] = make_uint4(o[j][0], o[j][1], o[j][2], o[j][3]);
-}
+    __shared__ float red_s[F32_NW / 2][F32_T * F32_RROW];
+    __shared__ uint8_t live_s[OCC_WIN];
+    __shared__ int skip_s[F32_NW];
+    static_assert(sizeof(red_s) >= SPLIT_SCRATCH_BYTES, "ranking scratch fits the reduction buffer");
 
-// 4 x 4 fp32: a renaming.
-template <>
-__device__ __forceinline__ void transpose_block<float>(const uint4 (&v)[4], uint4 (&u)[4])
-{
-    u[0] = make_uint4(v[0].x, v[1].x, v[2].x, v[3].x);
-    u[1] = make_uint4(v[0].y, v[1].y, v[2].y, v[3].y);
-    u[2] = make_uint4(v[0].z, v[1].z, v[2].z, v[3].z);
-    u[3] = make_uint4(v[0].w, v[1].w, v[2].w, v[3].w);
-}
-
-template <typename T>
-__global__ __launch_bounds__(NT) void bwd_weight_kernel(WeightParams p)
-{
-    constexpr int E = Elem<T>::E;
-    constexpr int BK = CH * E;                  // pixels per chunk
-    constexpr int CB = BM / E;                  // channel blocks
-    constexpr int NBLK = CB * (BK / E);         // E x E blocks per operand tile
-    constexpr int BPT = NBLK / HT;              // blocks per staging thread
-    static_assert(NBLK % HT == 0, "blocks must divide evenly");
-
-    __shared__ uint4 As[2][BM * CH];
-    __shared__ uint4 Bs[2][BN * CH];
-
-    const int tid = threadIdx.x;
-    const int lane = tid & 63, wave = tid >> 6;
-    const int wm = wave / WN, wn = wave % WN;
-    const bool stage_b = tid >= HT;             // wave-uniform role
-    const int st = stage_b ? tid - HT : tid;
-
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l16 = lane & 15, l4 = lane >> 4;
     const int RS = p.R * p.S;
     const int tiles = RS * p.ctiles * p.ktiles;
-    const int t = xcd_remap(blockIdx.x, gridDim.x);
+    const int wg = xcd_remap(blockIdx.x, gridDim.x);
+    const int sub = wg % (p.subc * p.subk), t = wg / (p.subc * p.subk);   // part of the tile, work item
     const int z = t / tiles;
     int rem = t - z * tiles;
     const int kt = rem % p.ktiles;
@@ -299,156 +270,172 @@ __global__ __launch_bounds__(NT) void bwd_weight_kernel(WeightParams p)
     const int ct = rem % p.ctiles;
     const int tap = rem / p.ctiles;
     const int r = tap / p.S, s = tap - r * p.S;
-    const int c0 = ct * BM, k0 = kt * BN;
+    const int c0 = ct * BM + sub % p.subc * F32_T, k0 = kt * BN + sub / p.subc * F32_T;
 
     if (blockIdx.x == 0 && tid == 0) {
         p.header[0] = p.mode_flags;
-        p.header[1] = 0;   // the readers' plan: 64-pixel chunks
+        p.header[1] = 0;   // the readers' plan: chunks of pixels
     }
-
-    floatx4 acc[FM][FN];
-#pragma unroll
-    for (int i = 0; i < FM; ++i)
-#pragma unroll
-        for (int j = 0; j < FN; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
-
-    const T* __restrict__ x = reinterpret_cast<const T*>(p.x);
-    const T* __restrict__ dy = reinterpret_cast<const T*>(p.dy);
-
-    uint4 rg[BPT][E];
-    int skipped = 0;
 
     const __amdgpu_buffer_rsrc_t rs_x = make_rsrc(p.x, p.x_bytes);
     const __amdgpu_buffer_rsrc_t rs_dy = make_rsrc(p.dy, p.dy_bytes);
-    constexpr uint32_t ESZ = sizeof(T);
+    const int cc = c0 + 4 * l16, kk = k0 + 4 * l16;
+    const bool c_in = cc < p.C, k_in = kk < p.K;
 
-    // Staging thread st owns blocks st + bi*HT: channel block cb, pixel block pb.
-    auto load = [&](int chunk) {
-        const int px_base = chunk * BK;
-#pragma unroll
-        for (int bi = 0; bi < BPT; ++bi) {
-            const int blk = st + bi * HT;
-            const int cb = blk % CB, pb = blk / CB;
-            const int pix0 = px_base + pb * E;
-            if (stage_b) {
-                const int kB = k0 + cb * E;
-#pragma unroll
-                for (int e = 0; e < E; ++e) {
-                    const int pix = pix0 + e;
-                    const bool ok = pix < p.npq && kB < p.K;
-                    rg[bi][e] = buf_load16(rs_dy, ok ? (uint32_t)(pix * p.K + kB) * ESZ : kOOB);
-                }
-            } else {
-                const int cA = c0 + cb * E;
-                // decode the block's first pixel once, then step along q
-                const uint32_t nq = fdiv((uint32_t)pix0, p.div_q);
-                int q = pix0 - (int)nq * p.Q;
-                const uint32_t nn = fdiv(nq, p.div_p);
-                int pp = (int)nq - (int)nn * p.P;
-                int n = (int)nn;
-#pragma unroll
-                for (int e = 0; e < E; ++e) {
-                    const int h = pp * p.stride_h - p.pad_h + r;
-                    const int w = q * p.stride_w - p.pad_w + s;
-                    const bool ok = n < p.N && cA < p.C && h >= 0 && h < p.H && w >= 0 && w < p.W;
-                    rg[bi][e] = buf_load16(rs_x, ok ? (uint32_t)(((n * p.H + h) * p.W + w) * p.C + cA) * ESZ : kOOB);
-                    if (++q == p.Q) {
-                        q = 0;
-                        if (++pp == p.P) { pp = 0; ++n; }
-                    }
-                }
-            }
+    // Walk over a chunk's pixels, 4 at a time, one per lane group: the lane's
+    // pixel, its column q and X column w, and the byte offsets of its loads
+    // (kOOB past the tensors; the steps added to that stay out of range).
+    // Along an image row they advance by constants; a lane that leaves its
+    // row decodes its pixel anew.
+    int pix = 0, q = 0, w = 0;
+    uint32_t x_off = kOOB, y_off = kOOB;
+    const uint32_t x_adv = (uint32_t)(4 * p.stride_w * p.C) * 4u, y_adv = (uint32_t)(4 * p.K) * 4u;
+    auto decode = [&]() {
+        const uint32_t nq = fdiv((uint32_t)pix, p.div_q);
+        q = pix - (int)nq * p.Q;
+        const uint32_t n = fdiv(nq, p.div_p);
+        const int h = ((int)nq - (int)n * p.P) * p.stride_h - p.pad_h + r;
+        w = q * p.stride_w - p.pad_w + s;
+        const bool in = pix < p.npq && c_in && (unsigned)h < (unsigned)p.H;
+        x_off = in ? (uint32_t)((((int)n * p.H + h) * p.W + w) * p.C + cc) * 4u : kOOB;
+    };
+    auto begin_chunk = [&](int chunk, int end) {
+        if (chunk < end) {
+            pix = chunk * F32_BK + l4;
+            decode();
+            y_off = pix < p.npq && k_in ? (uint32_t)(pix * p.K + kk) * 4u : kOOB;
+        } else {
+            q = w = -(1 << 30);   // never leaves its row
+            x_off = y_off = kOOB;
         }
     };
-
-    auto store = [&](int buf) {
-        uint4* dst = stage_b ? Bs[buf] : As[buf];
-#pragma unroll
-        for (int bi = 0; bi < BPT; ++bi) {
-            const int blk = st + bi * HT;
-            const int cb = blk % CB, pb = blk / CB;
-            uint4 u[E];
-            transpose_block<T>(rg[bi], u);
-#pragma unroll
-            for (int j = 0; j < E; ++j) {
-                const int row = cb * E + j;
-                dst[row * CH + (pb ^ swz(row))] = u[j];
-            }
-        }
+    auto load = [&](uint4& a, uint4& b) {
+        a = buf_load16(rs_x, (unsigned)w < (unsigned)p.W ? x_off : kOOB);
+        b = buf_load16(rs_dy, y_off);
+        pix += 4;
+        q += 4;
+        w += 4 * p.stride_w;
+        x_off += x_adv;
+        y_off += y_adv;   // (past the last pixel: past the buffer)
+        if (q >= p.Q) decode();
     };
 
-    auto compute = [&](int buf) {
-#pragma unroll
-        for (int kc = 0; kc < CH / 4; ++kc) {
-            const int chl = kc * 4 + (lane >> 4);
-            uint4 fa[FM], fb[FN];
-#pragma unroll
-            for (int i = 0; i < FM; ++i) {
-                const int row = wm * TM + i * 16 + (lane & 15);
-                fa[i] = As[buf][row * CH + (chl ^ swz(row))];
-            }
-#pragma unroll
-            for (int j = 0; j < FN; ++j) {
-                const int row = wn * TN + j * 16 + (lane & 15);
-                fb[j] = Bs[buf][row * CH + (chl ^ swz(row))];
-            }
-#pragma unroll
-            for (int i = 0; i < FM; ++i)
-#pragma unroll
-                for (int j = 0; j < FN; ++j) acc[i][j] = mfma_chunk(acc[i][j], fa[i], fb[j], T{});
-        }
-    };
-
-    // This split's chunk range (balanced over the tile's live chunks when
-    // skipping), with the liveness of its first OCC_WIN chunks read once into
-    // LDS so the loop tests them without a global read on its critical path.
-    // The ranking scratch borrows the second operand buffer, not yet in use.
-    __shared__ uint8_t live_s[OCC_WIN];
+    // This split's chunk range: the unskipped one unless the occupancy pass
+    // found a dead block (its flag carries this call's number).
     const int combo = tap * p.ctiles + ct;
-    int ch_begin, ch_end;
-    static_assert(sizeof(As[1]) >= SPLIT_SCRATCH_BYTES, "ranking scratch fits the second operand buffer");
-    const bool all_live = split_range(p, kt, combo, z, ch_begin, ch_end, live_s, reinterpret_cast<uint8_t*>(As[1]));
-    auto next_live = [&](int chunk) {
-        return all_live ? chunk : next_live_chunk(p, live_s, ch_begin, ch_end, kt, combo, chunk, skipped);
+    int ch_begin = min(p.nchunks, z * p.chunks_per_split);
+    int ch_end = min(p.nchunks, ch_begin + p.chunks_per_split);
+    uint32_t dflag = 0;
+    if (p.occ) dflag = __builtin_amdgcn_raw_buffer_load_b32(make_rsrc(p.header, 64), 4 * kDeadWord, 0, 0);
+    bool all_live = true;
+    if (p.occ && __builtin_amdgcn_readfirstlane(dflag) == p.gen) {
+        all_live = split_range(p, kt, combo, z, ch_begin, ch_end, live_s, reinterpret_cast<uint8_t*>(red_s));
+        __syncthreads();   // the scratch is free again
+    }
+    // The wave's next live chunk from c on (chunks c, c + 4, ...): each lane
+    // tests one, the ballot names the first live one.
+    int skipped = 0;
+    auto next_live = [&](int c) {
+        if (all_live) return c;
+        for (; c < ch_end; c += 64 * F32_NW) {
+            const int m = c + lane * F32_NW;
+            int v = 0;
+            if (m < ch_end) {
+                if (m - ch_begin < OCC_WIN) {
+                    v = live_s[m - ch_begin];
+                } else {
+                    v = p.occ[(int64_t)m * p.ktiles + kt];
+                    if (p.xlive) v &= p.xlive[(int64_t)m * RS * p.ctiles + combo];
+                }
+            }
+            const uint64_t live = __ballot(v != 0);
+            if (live != 0) {
+                const int f = __builtin_ctzll(live);
+                skipped += f;
+                return c + f * F32_NW;
+            }
+            skipped += min(64, (ch_end - c + F32_NW - 1) / F32_NW);
+        }
+        return c;
     };
 
-    int chunk = next_live(ch_begin);
-    int buf = 0;
-    if (chunk < ch_end) {
-        load(chunk);
-        store(0);
-    }
-    __syncthreads();
+    floatx4 acc[4][4];   // [A fragment][B fragment]
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+
+    constexpr int KS = F32_BK / 4;
+    uint4 a[KS], b[KS];
+    int chunk = next_live(ch_begin + wave);
+    begin_chunk(chunk, ch_end);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) load(a[ks], b[ks]);
     while (chunk < ch_end) {
-        const int next = next_live(chunk + 1);
-        if (next < ch_end) load(next);
-        compute(buf);
-        if (next < ch_end) store(buf ^ 1);
-        __syncthreads();
-        buf ^= 1;
+        const int next = next_live(chunk + F32_NW);
+        begin_chunk(next, ch_end);
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            const uint32_t av[4] = {a[ks].x, a[ks].y, a[ks].z, a[ks].w};
+            const uint32_t bv[4] = {b[ks].x, b[ks].y, b[ks].z, b[ks].w};
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(av[i]), __uint_as_float(bv[j]),
+                                                                     acc[i][j], 0, 0, 0);
+            load(a[ks], b[ks]);   // (past the range: zeros, no traffic)
+        }
         chunk = next;
     }
 
-    if (tid == 0) {
-        p.skip_slots[blockIdx.x] = skipped;
-        p.work_slots[t] = ch_end - ch_begin - skipped;
+    // acc[i][j][v] is column 4 (4 (lane / 16) + v) + i of output channel
+    // 4 (lane % 16) + j: the four fragments of one v are four consecutive
+    // columns.  Waves 2 and 3 hand their sums to 0 and 1, whose own two are
+    // added on the way out.
+    auto slot = [&](int w, int j, int v) {
+        return reinterpret_cast<float4*>(&red_s[w][(4 * l16 + j) * F32_RROW + 16 * l4 + 4 * v]);
+    };
+    static_assert(F32_NW == 4, "two rounds of two");
+    if (lane == 0) skip_s[wave] = skipped;
+    if (wave >= 2) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                *slot(wave - 2, j, v) = make_float4(acc[0][j][v], acc[1][j][v], acc[2][j][v], acc[3][j][v]);
     }
-
-    // Epilogue: lane holds channels c0 + wm*TM + i*16 + 4*(lane/16) + v of
-    // output channel k0 + wn*TN + j*16 + lane%16; written to [z][k][tap][c].
-    // Buffer stores over this split's [K][RS][C] region: lanes past K or C
-    // get offset kOOB and their stores are dropped (no branches).
-    const uint32_t split_bytes = (uint32_t)p.K * RS * p.C * 4u;
-    const __amdgpu_buffer_rsrc_t rs_out = make_rsrc(p.out + (int64_t)z * p.K * RS * p.C, split_bytes);
+    __syncthreads();
+    if (wave < 2) {
+        // (a lane reads and overwrites the same places)
 #pragma unroll
-    for (int j = 0; j < FN; ++j) {
-        const int k = k0 + wn * TN + j * 16 + (lane & 15);
+        for (int j = 0; j < 4; ++j)
 #pragma unroll
-        for (int i = 0; i < FM; ++i) {
-            const int c = c0 + wm * TM + i * 16 + 4 * (lane >> 4);
-            const uint32_t off = (k < p.K && c < p.C) ? (uint32_t)((k * RS + tap) * p.C + c) * 4u : kOOB;
-            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[i][j]), rs_out, off, 0, 0);
-        }
+            for (int v = 0; v < 4; ++v) {
+                const float4 o = *slot(wave, j, v);
+                *slot(wave, j, v) = make_float4(acc[0][j][v] + o.x, acc[1][j][v] + o.y, acc[2][j][v] + o.z,
+                                                acc[3][j][v] + o.w);
+            }
+    }
+    __syncthreads();
+    const __amdgpu_buffer_rsrc_t rs_out =
+        make_rsrc(p.out + (int64_t)z * p.K * RS * p.C, (uint32_t)p.K * RS * p.C * 4u);
+    for (int o = tid; o < F32_T * F32_T / 4; o += F32_NW * 64) {
+        const int kl = o >> 4, cl = 4 * (o & 15);
+        float4 sum = *reinterpret_cast<const float4*>(&red_s[0][kl * F32_RROW + cl]);
+        const float4 v = *reinterpret_cast<const float4*>(&red_s[1][kl * F32_RROW + cl]);
+        sum.x += v.x; sum.y += v.y; sum.z += v.z; sum.w += v.w;
+        const int k = k0 + kl, c = c0 + cl;
+        const uint32_t off = (k < p.K && c < p.C) ? (uint32_t)((k * RS + tap) * p.C + c) * 4u : kOOB;
+        __builtin_amdgcn_raw_buffer_store_b128(
+            u32x4{__float_as_uint(sum.x), __float_as_uint(sum.y), __float_as_uint(sum.z), __float_as_uint(sum.w)},
+            rs_out, off, 0, 0);
+    }
+    if (sub == 0 && tid == 0) {
+        int n = 0;
+        for (int w = 0; w < F32_NW; ++w) n += skip_s[w];
+        p.skip_slots[t] = n;
+        p.work_slots[t] = ch_end - ch_begin - n;
     }
 }
 
@@ -1052,7 +1039,7 @@ __global__ __launch_bounds__(RW_NT) void bwd_weight_rows_kernel(WeightParams p)
 
 int weight_tile_channels() { return BM; }
 int weight_tile_k() { return BN; }
-int weight_chunk(int dtype) { return CH * (dtype == 1 ? 8 : 4); }
+int weight_chunk(int dtype) { return dtype == 1 ? TR_BK : F32_BK; }
 
 hipError_t launch_bwd_weight(int dtype, const WeightParams& p, hipStream_t stream, const ProfEvents& ev)
 {
@@ -1071,13 +1058,14 @@ hipError_t launch_bwd_weight(int dtype, const WeightParams& p, hipStream_t strea
         }
         return e_launch;
     }
-    const dim3 grid(nb), block(dtype != 1 ? NT : p.bk == 64 ? WTile<64>::NT : WTile<256>::NT);
-    if (dtype == 1) {
-        if (p.bk == 64) e_launch = launch_timed(bwd_weight_tr_kernel<64>, grid, block, stream, ev, p);
-        else if (p.bk == 128) e_launch = launch_timed(bwd_weight_tr_kernel<128>, grid, block, stream, ev, p);
-        else e_launch = launch_timed(bwd_weight_tr_kernel<256>, grid, block, stream, ev, p);
+    if (dtype != 1) {
+        if (p.tpg != 1 || p.subc < 1 || p.subk < 1) return hipErrorInvalidValue;
+        return launch_timed(bwd_weight_f32_kernel, dim3(nb * p.subc * p.subk), dim3(F32_NW * 64), stream, ev, p);
     }
-    else e_launch = launch_timed(bwd_weight_kernel<float>, grid, block, stream, ev, p);
+    const dim3 grid(nb), block(p.bk == 64 ? WTile<64>::NT : WTile<256>::NT);
+    if (p.bk == 64) e_launch = launch_timed(bwd_weight_tr_kernel<64>, grid, block, stream, ev, p);
+    else if (p.bk == 128) e_launch = launch_timed(bwd_weight_tr_kernel<128>, grid, block, stream, ev, p);
+    else e_launch = launch_timed(bwd_weight_tr_kernel<256>, grid, block, stream, ev, p);
     return e_launch;
 }
 

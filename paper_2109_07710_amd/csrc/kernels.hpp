@@ -164,6 +164,7 @@ struct WeightParams {
     int bk;                  // output channels per tile (64, 128, 256)
     int tpg, tgroups;        // filter taps per 256-column channel tile, and tap groups
     int cg;                  // channel columns per packed tap (C when packed, else 256)
+    int subc, subk;          // fp32: 64-column and 64-channel parts of a tile, a workgroup each
     int rows;                // row-window kernel: chunks are output rows, tgroups are 128-column segments
     int mode_flags;
     uint32_t x_bytes, dy_bytes;

@@ -256,7 +256,7 @@ int fwd_as_data_desc(const cbw_conv_desc* d, cbw_conv_desc* out)
 
 int weight_tile_k_for(const cbw_conv_desc* d)
 {
-    if (d->dtype != CBW_BF16) return kWeightTileK;   // the fp32 kernel keeps 256 x 256 tiles
+    if (d->dtype != CBW_BF16) return kWeightTileK;   // fp32: 256 x 256 tiles in 64 x 64 parts
     if (d->K <= 64) return 64;
     if (d->K <= 128) return 128;
     return kWeightTileK;
@@ -277,6 +277,32 @@ bool weight_rows_eligible(const cbw_conv_desc* d)
 {
     return d->dtype == CBW_BF16 && d->stride_h == 1 && d->stride_w == 1 && d->R <= 3 && d->S <= 3 &&
            d->C % 64 == 0 && d->K % 64 == 0 && d->C <= 128 && d->K <= 128;
+}
+
+// Splits of the fp32 weight gradient: `wgs` workgroups of four waves per
+// split.  A CU runs its share one wave per SIMD each, 1.9 us of matrix work
+// per chunk and wave, up to three workgroups at a time; starting and
+// finishing takes about 3 us per three; every split writes and reads back
+// the whole gradient at about 4 TB/s.  The cheapest count by that model:
+// as many splits as fill the CUs once left them idle where the quotient is
+// small (256 -> 256 channels, 28 x 28, N = 8: 144 workgroups a split, one
+// split 128 us, five 94, with workgroups of eight waves).
+static int f32_weight_splits(const cbw_conv_desc* d, int64_t wgs, int nchunks, int max_split)
+{
+    const double part = (double)d->K * d->R * d->S * d->C * 8 / 4e6;
+    int best = 1;
+    double best_cost = 0;
+    for (int ns = 1; ns <= max_split && ns <= 3 * CBW_NUM_CUS; ++ns) {
+        const int per = (nchunks + ns - 1) / ns;
+        if ((nchunks + per - 1) / per != ns) continue;   // the same ranges as fewer splits
+        const int64_t w = (wgs * ns + CBW_NUM_CUS - 1) / CBW_NUM_CUS;
+        const double cost = 1.9 * w * ((per + 3) / 4) + 3.0 * ((w + 2) / 3) + part * ns;
+        if (ns == 1 || cost < best_cost) {
+            best = ns;
+            best_cost = cost;
+        }
+    }
+    return best;
 }
 
 int plan_weight(const cbw_conv_desc* d, WeightPlan* out, bool allow_rows)
@@ -307,12 +333,18 @@ int plan_weight(const cbw_conv_desc* d, WeightPlan* out, bool allow_rows)
     }
     p.ktiles = (d->K + p.bk - 1) / p.bk;
     const int tiles = p.tgroups * p.ctiles * p.ktiles;
+    if (d->dtype != CBW_BF16) {
+        // the parts of a 256 x 256 tile that hold channels
+        p.subc = (std::min(d->C, kWeightTileC) + 63) / 64;
+        p.subk = (std::min(d->K, kWeightTileK) + 63) / 64;
+    }
     // as many splits as fit in one round of resident workgroups
-    int nsplit = kWeightSlots / tiles;
+    int nsplit = kWeightSlots / (tiles * p.subc * p.subk);
     int max_split = p.nchunks / 4;  // at least four chunks per workgroup
     if (max_split < 1) max_split = 1;
     if (nsplit > max_split) nsplit = max_split;
     if (nsplit < 1) nsplit = 1;
+    if (d->dtype != CBW_BF16) nsplit = f32_weight_splits(d, tiles * p.subc * p.subk, p.nchunks, max_split);
     p.chunks_per_split = (p.nchunks + nsplit - 1) / nsplit;
     p.nsplit = (p.nchunks + p.chunks_per_split - 1) / p.chunks_per_split;
     p.grid = tiles * p.nsplit;

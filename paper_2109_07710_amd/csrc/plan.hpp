@@ -94,6 +94,7 @@ struct WeightPlan {
     int chunk = 0;          // pixels per occupancy chunk (64, or Q for the row-window kernel)
     int64_t npq = 0;
     int bk = 0, tpg = 1, tgroups = 0;   // output-channel tile width, taps per group, tap groups
+    int subc = 1, subk = 1;             // fp32: workgroups per tile along its channels and output channels
     int cg = 0;                         // channel columns per packed tap (C, or 256 without packing)
     int nchunks = 0, ctiles = 0, ktiles = 0, nsplit = 0, chunks_per_split = 0, grid = 0;
     int nparts = 0;         // partials the reduction sums

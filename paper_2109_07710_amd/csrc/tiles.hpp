@@ -12,12 +12,6 @@
 #ifndef CBW_DW_BN
 #define CBW_DW_BN 256   // weight gradient: output channels k per tile
 #endif
-#ifndef CBW_DW_WM
-#define CBW_DW_WM 2
-#endif
-#ifndef CBW_DW_WN
-#define CBW_DW_WN 4
-#endif
 #ifndef CBW_DW_OCC
 #define CBW_DW_OCC 1
 #endif
