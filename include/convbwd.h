@@ -243,7 +243,8 @@ int conv_bwd_weight_sparse_x(const cbw_conv_desc* desc, const void* X, const voi
  * the device; a dense tiling split by the planner) adds its split
  * reduction: three or four launches.  With the row-window or pointwise data
  * gradient: the data GEMM, the weight GEMM and one reduction launch.
- * NCHW tensors are served by the two separate calls.  Arguments as in the
+ * NCHW tensors are transposed into the workspace once for both gradients
+ * and dX is transposed back.  Arguments as in the
  * separate calls (X, dY, W, dX, dW and the footprints 16-byte aligned);
  * dX = NULL computes the weight gradient alone (a first layer, whose input
  * needs no gradient; W may then be NULL too); flags: CBW_FLAG_NO_SKIP,

@@ -221,6 +221,13 @@ int last_weight_plan(const cbw_conv_desc* desc, const void* workspace, size_t wo
     return CBW_OK;
 }
 
+// The NHWC dX of an NCHW call into the caller's dX.
+hipError_t launch_dx_out(const cbw_conv_desc* desc, const void* dX, void* out, hipStream_t s)
+{
+    const LayoutJob job{dX, out, false, desc->N, desc->H * desc->W, desc->C};
+    return launch_layout(desc->dtype, &job, 1, s);
+}
+
 int run_bwd_data(const cbw_conv_desc* desc, const void* dY, const void* W, const uint32_t* x_mask, void* dX,
                  void* ws, size_t ws_bytes, uint32_t flags, void* stream, bool masked, bool no_split = false)
 {
@@ -242,16 +249,13 @@ int run_bwd_data(const cbw_conv_desc* desc, const void* dY, const void* W, const
         // the kernels read an NHWC copy of dY (and an NHWC-order footprint)
         // and write an NHWC dX, transposed into the caller's dX at the end
         void* tdy = at<void>(ws, plan.t_dy);
-        if ((e = launch_transpose(desc->dtype, dY, tdy, desc->N, desc->K, desc->P * desc->Q, s)) != hipSuccess)
-            return hip_status(e);
+        uint32_t* tmask = masked ? at<uint32_t>(ws, plan.t_mask) : nullptr;
+        const LayoutJob in[] = {{dY, tdy, false, desc->N, desc->K, desc->P * desc->Q},
+                                {x_mask, tmask, true, desc->N, desc->C, desc->H * desc->W}};
+        if ((e = launch_layout(desc->dtype, in, 2, s)) != hipSuccess) return hip_status(e);
         dY = tdy;
         dX = at<void>(ws, plan.t_dx);
-        if (masked) {
-            uint32_t* t = at<uint32_t>(ws, plan.t_mask);
-            if ((e = launch_bits_nchw_to_nhwc(x_mask, t, desc->N, desc->C, desc->H * desc->W, s)) != hipSuccess)
-                return hip_status(e);
-            x_mask = t;
-        }
+        if (masked) x_mask = tmask;
     }
     int* header = at<int>(ws, plan.header);
     void* wt = at<void>(ws, plan.wt);
@@ -279,8 +283,7 @@ int run_bwd_data(const cbw_conv_desc* desc, const void* dY, const void* W, const
         if (e != hipSuccess) return hip_status(e);
         if ((e = launch_bwd_data(desc->dtype, mode, p, s, prof_events(0))) != hipSuccess) return hip_status(e);
     }
-    if (dX != dX_out)
-        e = launch_transpose(desc->dtype, dX, dX_out, desc->N, desc->H * desc->W, desc->C, s);
+    if (dX != dX_out) e = launch_dx_out(desc, dX, dX_out, s);
     return hip_status(e);
 }
 
@@ -594,6 +597,34 @@ static WeightParams weight_gemm_params(const cbw_conv_desc* desc, const WeightPl
     return p;
 }
 
+// NHWC copies of an NCHW call's weight-gradient inputs in its workspace (the
+// footprints where they are used), and the conversions that fill them: X,
+// dY, dY's footprint, X's footprint.
+struct WeightInputs {
+    const void *x, *dy;
+    const uint32_t *dy_mask, *x_mask;
+    LayoutJob jobs[4];
+};
+static WeightInputs weight_inputs(const cbw_conv_desc* desc, const WeightPlan& plan, const void* X, const void* dY,
+                                  const uint32_t* x_mask, const uint32_t* dy_mask, void* workspace, bool skip,
+                                  bool x_skip)
+{
+    WeightInputs in{};
+    void* tx = at<void>(workspace, plan.t_x);
+    void* tdy = at<void>(workspace, plan.t_dy);
+    uint32_t* ty = skip && dy_mask ? at<uint32_t>(workspace, plan.t_dymask) : nullptr;
+    uint32_t* tm = skip && x_skip && x_mask ? at<uint32_t>(workspace, plan.xbits) : nullptr;
+    in.x = tx;
+    in.dy = tdy;
+    in.dy_mask = ty;
+    in.x_mask = tm;
+    in.jobs[0] = {X, tx, false, desc->N, desc->C, desc->H * desc->W};
+    in.jobs[1] = {dY, tdy, false, desc->N, desc->K, desc->P * desc->Q};
+    in.jobs[2] = {dy_mask, ty, true, desc->N, desc->K, desc->P * desc->Q};
+    in.jobs[3] = {x_mask, tm, true, desc->N, desc->C, desc->H * desc->W};
+    return in;
+}
+
 // Weight gradient; x_skip also skips blocks whose X operand is all zero.
 static int run_weight(const cbw_conv_desc* desc, const void* X, const void* dY, const uint32_t* x_mask,
                const uint32_t* dy_mask, bool x_skip, float* dW, void* workspace, size_t workspace_bytes,
@@ -614,25 +645,12 @@ static int run_weight(const cbw_conv_desc* desc, const void* X, const void* dY, 
     hipError_t e;
     if (desc->act_layout == CBW_NCHW) {
         // the kernels read NHWC copies of X and dY (and NHWC-order footprints)
-        void* tx = at<void>(workspace, plan.t_x);
-        void* tdy = at<void>(workspace, plan.t_dy);
-        if ((e = launch_transpose(desc->dtype, X, tx, desc->N, desc->C, desc->H * desc->W, s)) != hipSuccess ||
-            (e = launch_transpose(desc->dtype, dY, tdy, desc->N, desc->K, desc->P * desc->Q, s)) != hipSuccess)
-            return hip_status(e);
-        X = tx;
-        dY = tdy;
-        if (skip && dy_mask) {
-            uint32_t* t = at<uint32_t>(workspace, plan.t_dymask);
-            if ((e = launch_bits_nchw_to_nhwc(dy_mask, t, desc->N, desc->K, desc->P * desc->Q, s)) != hipSuccess)
-                return hip_status(e);
-            dy_mask = t;
-        }
-        if (skip && x_skip && x_mask) {
-            uint32_t* t = at<uint32_t>(workspace, plan.xbits);
-            if ((e = launch_bits_nchw_to_nhwc(x_mask, t, desc->N, desc->C, desc->H * desc->W, s)) != hipSuccess)
-                return hip_status(e);
-            x_mask = t;
-        }
+        const WeightInputs in = weight_inputs(desc, plan, X, dY, x_mask, dy_mask, workspace, skip, x_skip);
+        if ((e = launch_layout(desc->dtype, in.jobs, 4, s)) != hipSuccess) return hip_status(e);
+        X = in.x;
+        dY = in.dy;
+        dy_mask = in.dy_mask;
+        x_mask = in.x_mask;
     }
     if (skip) {
         const uint32_t* xbits = x_mask;
@@ -664,8 +682,8 @@ static int run_weight(const cbw_conv_desc* desc, const void* X, const void* dY, 
 // gradient the weight GEMM, the data GEMM (the weight gradient's split-K
 // reduction in its tail workgroups) and, when the data gradient may split,
 // its split reduction; with the row-window or pointwise data gradient the
-// data GEMM, the weight GEMM and one reduction launch.  NCHW: the two
-// separate calls on the two parts of the workspace.
+// data GEMM, the weight GEMM and one reduction launch.  NCHW: the same on
+// NHWC copies of the inputs, dX transposed back at the end.
 static int run_bwd_both(const cbw_conv_desc* desc, const void* X, const void* dY, const void* W,
                         const uint32_t* x_mask, const uint32_t* dy_mask, void* dX, float* dW, void* ws,
                         size_t ws_bytes, uint32_t flags, void* stream)
@@ -693,13 +711,27 @@ static int run_bwd_both(const cbw_conv_desc* desc, const void* X, const void* dY
     if (!want_dx)
         return run_weight(desc, X, dY, x_skip ? x_mask : nullptr, dy_mask, x_skip, dW, wws, total - off,
                           flags & CBW_FLAG_NO_SKIP, stream);
-    if (desc->act_layout == CBW_NCHW) {
-        st = run_bwd_data(desc, dY, W, x_mask, dX, ws, off, flags & CBW_FLAG_NO_SKIP, stream, masked);
-        if (st != CBW_OK) return st;
-        return run_weight(desc, X, dY, x_skip ? x_mask : nullptr, dy_mask, x_skip, dW, wws, total - off,
-                          flags & CBW_FLAG_NO_SKIP, stream);
-    }
     hipStream_t s = static_cast<hipStream_t>(stream);
+    void* const dX_out = dX;
+    if (desc->act_layout == CBW_NCHW) {
+        // one NHWC copy of every input, in one launch; both gradients read
+        // the weight part's dY, and X's footprint lands in the data part
+        WeightInputs in = weight_inputs(desc, wplan, X, dY, nullptr, dy_mask, wws, skip, false);
+        uint32_t* tmask = masked ? at<uint32_t>(ws, dplan.t_mask) : nullptr;
+        in.jobs[3] = {x_mask, tmask, true, desc->N, desc->C, desc->H * desc->W};
+        hipError_t el = launch_layout(desc->dtype, in.jobs, 4, s);
+        if (el != hipSuccess) return hip_status(el);
+        X = in.x;
+        dY = in.dy;
+        dy_mask = in.dy_mask;
+        x_mask = tmask;
+        dX = at<void>(ws, dplan.t_dx);
+    }
+    // dX to the caller's layout, where that is not the kernels'
+    auto finish = [&](hipError_t el) {
+        if (el == hipSuccess && dX != dX_out) el = launch_dx_out(desc, dX, dX_out, s);
+        return hip_status(el);
+    };
     const bool tiled = !dplan.rows && !dplan.pw;   // the tiled GEMM (else a dedicated kernel)
     const bool gather = tiled && data_gathers(dplan, masked, flags);
     const int mode = dplan.rows ? MODE_ROWS
@@ -742,8 +774,7 @@ static int run_bwd_both(const cbw_conv_desc* desc, const void* X, const void* dY
         dp.dw_red = rp;
         if ((e = launch_bwd_data(desc->dtype, mode, dp, s, prof_events(0), false)) != hipSuccess) return hip_status(e);
         const bool dx_reduce = mode == MODE_GATHER || dplan.split > 1;
-        if (!dx_reduce) return CBW_OK;
-        return hip_status(launch_bwd_reduce(desc->dtype, mode, dp, true, ReduceParams{}, s));
+        return finish(dx_reduce ? launch_bwd_reduce(desc->dtype, mode, dp, true, ReduceParams{}, s) : hipSuccess);
     }
     if (dplan.rows) {
         const DataRowsParams rwp = data_rows_params(desc, dplan, dY, wt, x_mask, dX, ws, skip);
@@ -754,7 +785,7 @@ static int run_bwd_both(const cbw_conv_desc* desc, const void* X, const void* dY
     }
     if (e != hipSuccess) return hip_status(e);
     if ((e = launch_bwd_weight(desc->dtype, wp, s, prof_events(1))) != hipSuccess) return hip_status(e);
-    return hip_status(launch_bwd_reduce(desc->dtype, mode, dp, false, rp, s));
+    return finish(launch_bwd_reduce(desc->dtype, mode, dp, false, rp, s));
 }
 
 int conv_bwd_data_elementwise(const cbw_conv_desc* desc, const void* dY, const void* W, const uint32_t* x_mask,
