@@ -542,6 +542,7 @@ static OccParams weight_occ_params(const cbw_conv_desc* desc, const WeightPlan& 
     op.cpw = std::max(1, std::min(std::min((x_skip ? 256 : 2048) / per_chunk, spread),
                                   1024 / std::max(plan.ktiles, ncombo)));
     op.dtype = desc->dtype;
+    op.pmask = plan.pmask.bytes && dy_mask ? at<uint64_t>(workspace, plan.pmask) : nullptr;
     if (x_skip) {
         op.xbits = xbits;
         op.xlive = at<uint8_t>(workspace, plan.xlive);
@@ -561,14 +562,15 @@ static OccParams weight_occ_params(const cbw_conv_desc* desc, const WeightPlan& 
 
 // Kernel parameters of the weight-gradient GEMM on NHWC X and dY.
 static WeightParams weight_gemm_params(const cbw_conv_desc* desc, const WeightPlan& plan, const void* X,
-                                       const void* dY, float* dW, void* workspace, bool skip, bool x_skip,
-                                       uint32_t flags)
+                                       const void* dY, const uint32_t* dy_mask, float* dW, void* workspace,
+                                       bool skip, bool x_skip, uint32_t flags)
 {
     WeightParams p{};
     p.x = X;
     p.dy = dY;
     p.out = plan.direct ? dW : at<float>(workspace, plan.partials);
     p.occ = skip ? at<uint8_t>(workspace, plan.occ) : nullptr;
+    p.pmask = skip && dy_mask && plan.pmask.bytes ? at<uint64_t>(workspace, plan.pmask) : nullptr;
     p.xlive = skip && x_skip ? at<uint8_t>(workspace, plan.xlive) : nullptr;
     p.work_slots = at<int32_t>(workspace, plan.work_slots);
     p.skip_slots = at<int32_t>(workspace, plan.skip_slots);
@@ -666,7 +668,7 @@ static int run_weight(const cbw_conv_desc* desc, const void* X, const void* dY, 
         const OccParams op = weight_occ_params(desc, plan, dY, dy_mask, x_skip, xbits, workspace, gen);
         if ((e = launch_occupancy(op, s)) != hipSuccess) return hip_status(e);
     }
-    WeightParams p = weight_gemm_params(desc, plan, X, dY, dW, workspace, skip, x_skip, flags);
+    WeightParams p = weight_gemm_params(desc, plan, X, dY, dy_mask, dW, workspace, skip, x_skip, flags);
     p.gen = gen;
     if ((e = launch_bwd_weight(desc->dtype, p, s, prof_events(1))) != hipSuccess) return hip_status(e);
     if (!plan.direct) {
@@ -749,7 +751,7 @@ static int run_bwd_both(const cbw_conv_desc* desc, const void* X, const void* dY
                                     desc->w_layout == CBW_KRSC, header, mode, gather ? &cp : nullptr, s,
                                     skip ? &op : nullptr);
     if (e != hipSuccess) return hip_status(e);
-    WeightParams wp = weight_gemm_params(desc, wplan, X, dY, dW, wws, skip, x_skip, flags & CBW_FLAG_NO_SKIP);
+    WeightParams wp = weight_gemm_params(desc, wplan, X, dY, dy_mask, dW, wws, skip, x_skip, flags & CBW_FLAG_NO_SKIP);
     wp.gen = gen;
     ReduceParams rp{};
     if (!wplan.direct) {

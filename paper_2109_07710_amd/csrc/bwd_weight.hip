@@ -21,6 +21,7 @@
 #include "kernels.hpp"
 #include "tiles.hpp"
 
+#include <type_traits>
 
 namespace cbw {
 
@@ -29,6 +30,7 @@ namespace {
 constexpr int BM = CBW_DW_BM;   // channels c per tile
 constexpr int BN = CBW_DW_BN;   // output channels k per tile
 constexpr int F32_BK = 32;      // pixels per fp32 chunk
+constexpr int TR_BK = 64;       // pixels per bf16 step (chunk)
 constexpr int OCC_WIN = 1024;   // occupancy bytes cached per workgroup
 
 // The chunk range [begin, end) of split z of a weight-gradient tile, with the
@@ -187,6 +189,81 @@ __device__ bool split_range(const WeightParams& p, int kt, int combo, int z, int
     __syncthreads();
     return false;
 }
+// Pixel compaction.  Where whole pixels of dY are dead (footprints shared
+// by the channels), most 64-pixel blocks still hold a live one, and a block
+// costs the same however few of its pixels are live.  When the live pixels of
+// the k tile fit half as many blocks as are live, the splits share out blocks
+// of live pixels instead: rank r of the k tile's live pixels in pixel order
+// belongs to block r / 64, and split z takes ceil(blocks / nsplit) of them in
+// order, its pixels listed in list[] (npq, past the last pixel, fills the
+// last block: it reads zeros).  Products left out are exactly zero.  Half is
+// well past the break-even: listing costs a few microseconds a launch, a
+// block about 1.3 us.  Called by the whole workgroup; scratch as in
+// split_range.  False (nothing changed): not worth it, or more pixels per
+// split than list[] holds.  512 channels, 14 x 14, N = 128, 10% of the
+// pixels live in every channel: 100 us for 81% of the blocks, 31 us here.
+constexpr int LIST_CAP = 7168;
+__device__ bool compact_range(const WeightParams& p, int kt, int combo, int z, int& begin, int& end, int& nblocks,
+                              int* list, uint8_t* scratch)
+{
+    const int nch = p.nchunks, T = blockDim.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nw = T >> 6;
+    const int ncombo = p.tgroups * p.ctiles;
+    const uint64_t* m = p.pmask + (int64_t)kt * nch;
+    int* wsum = reinterpret_cast<int*>(scratch);   // [0, 16): live pixels per wave, [16, 32): live chunks
+    const int per = (nch + T - 1) / T;
+    const int s0 = min(nch, tid * per), s1 = min(nch, s0 + per);
+    int cnt = 0, chunks = 0;
+    for (int c = s0; c < s1; ++c) {
+        const uint64_t v = m[c];
+        cnt += __popcll(v);
+        chunks += v != 0 && (!p.xlive || p.xlive[(int64_t)c * ncombo + combo]) ? 1 : 0;
+    }
+    int incl = cnt;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int v = __shfl_up(incl, off, 64);
+        if (lane >= off) incl += v;
+        chunks += __shfl_xor(chunks, off);
+    }
+    if (lane == 63) {
+        wsum[wave] = incl;
+        wsum[16 + wave] = chunks;
+    }
+    __syncthreads();
+    int total = 0, live = 0;
+    for (int w = 0; w < nw; ++w) {
+        const int v = wsum[w];
+        if (w < wave) incl += v;
+        total += v;
+        live += wsum[16 + w];
+    }
+    total = __builtin_amdgcn_readfirstlane(total);
+    live = __builtin_amdgcn_readfirstlane(live);
+    const int blocks = (total + TR_BK - 1) / TR_BK, share = (blocks + p.nsplit - 1) / p.nsplit;
+    if (2 * blocks > live || share * TR_BK > LIST_CAP) {
+        __syncthreads();   // the scratch is free again
+        return false;
+    }
+    begin = min(z * share, blocks);
+    end = min(begin + share, blocks);
+    nblocks = blocks;
+    const int r0 = begin * TR_BK, r1 = min(end * TR_BK, total);
+    for (int i = r1 - r0 + tid; i < (end - begin) * TR_BK; i += T) list[i] = p.npq;
+    int rank = incl - cnt;
+    for (int c = s0; c < s1 && rank < r1; ++c) {
+        uint64_t v = m[c];
+        const int n = __popcll(v);
+        if (rank + n <= r0) {
+            rank += n;
+            continue;
+        }
+        for (; v != 0; v &= v - 1, ++rank)
+            if (rank >= r0 && rank < r1) list[rank - r0] = c * TR_BK + __builtin_ctzll(v);
+    }
+    __syncthreads();
+    return true;
+}
+
 // The first live chunk in [chunk, end) (end when there is none), counting the
 // dead chunks passed in skipped.  Each lane tests one of 64 consecutive
 // chunks and the wave's ballot names the first live one, so a long run of
@@ -467,7 +544,6 @@ constexpr int TR_NT = 1024;            // 16 waves (four per SIMD): more waves h
 #ifndef CBW_DW_TR64_NT
 #define CBW_DW_TR64_NT 1024
 #endif
-constexpr int TR_BK = 64;              // pixels per step
 constexpr int TR_ROW = BM / 8;         // 16-byte chunks per LDS row (one pixel)
 static_assert(BM == 256 && BN == 256, "the natural-layout kernel assumes 256-wide rows");
 
@@ -498,6 +574,7 @@ __global__ __launch_bounds__(WTile<BKT>::NT) void bwd_weight_tr_kernel(WeightPar
     constexpr int TM = WTile<BKT>::TM, TN = WTile<BKT>::TN, FM = WTile<BKT>::FM, FN = WTile<BKT>::FN;
     __shared__ uint4 As[2][TR_BK * TR_ROW];
     __shared__ uint4 Bs[2][TR_BK * TR_ROW];
+    __shared__ int list_s[LIST_CAP];   // compacted: the split's live pixels
 
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
@@ -550,10 +627,12 @@ __global__ __launch_bounds__(WTile<BKT>::NT) void bwd_weight_tr_kernel(WeightPar
         xch[j] = (tl < p.tpg && tap < RS && c0 + cc < p.C) ? (uint32_t)(c0 + cc) * ESZ : kOOB;
         dych[j] = (8 * lc < BKT && k0 + 8 * lc < p.K) ? (uint32_t)(k0 + 8 * lc) * ESZ : kOOB;
     }
-    auto set_chunk = [&](int chunk) {
+    bool compact = false;   // blocks of listed live pixels instead of chunks
+    int list0 = 0;          // first block of the list
+    auto set_chunk = [&](int chunk, auto listed) {
 #pragma unroll
         for (int j = 0; j < TR_IA; ++j) {
-            const int pix = chunk * TR_BK + rowj[j];
+            const int pix = listed.value ? list_s[(chunk - list0) * TR_BK + rowj[j]] : chunk * TR_BK + rowj[j];
             dpix[j] = pix;
             const uint32_t nq = fdiv((uint32_t)pix, p.div_q);
             xq[j] = pix - (int)nq * p.Q;
@@ -639,7 +718,7 @@ __global__ __launch_bounds__(WTile<BKT>::NT) void bwd_weight_tr_kernel(WeightPar
     static_assert(sizeof(As[1]) >= SPLIT_SCRATCH_BYTES, "ranking scratch fits the second operand buffer");
     int chunk = ch_begin;
     if (chunk < ch_end) {
-        set_chunk(chunk);
+        set_chunk(chunk, std::false_type{});
         load(0);
     }
     uint32_t dflag = 0;
@@ -649,10 +728,19 @@ __global__ __launch_bounds__(WTile<BKT>::NT) void bwd_weight_tr_kernel(WeightPar
     bool all_live = true;
     int skipped = 0;
     if (p.occ && __builtin_amdgcn_readfirstlane(dflag) == p.gen) {
-        all_live = split_range(p, kt, combo, z, ch_begin, ch_end, live_s, reinterpret_cast<uint8_t*>(As[1]));
+        if (p.pmask) {
+            int nblocks = 0;
+            compact = compact_range(p, kt, combo, z, ch_begin, ch_end, nblocks, list_s,
+                                    reinterpret_cast<uint8_t*>(As[1]));
+            list0 = ch_begin;
+            if (compact && z == 0) skipped = p.nchunks - nblocks;   // (the splits' sum: blocks not executed)
+        }
+        if (!compact)
+            all_live = split_range(p, kt, combo, z, ch_begin, ch_end, live_s, reinterpret_cast<uint8_t*>(As[1]));
         chunk = all_live ? ch_begin : next_live_chunk(p, live_s, ch_begin, ch_end, kt, combo, ch_begin, skipped);
         if (chunk < ch_end) {
-            set_chunk(chunk);
+            if (compact) set_chunk(chunk, std::true_type{});
+            else set_chunk(chunk, std::false_type{});
             load(0);
         }
         wait_vmem();
@@ -661,11 +749,27 @@ __global__ __launch_bounds__(WTile<BKT>::NT) void bwd_weight_tr_kernel(WeightPar
     auto next_live = [&](int c) {
         return all_live ? c : next_live_chunk(p, live_s, ch_begin, ch_end, kt, combo, c, skipped);
     };
+    // (the listed form is a loop of its own: as a branch of the usual one it
+    // cost every layer 1.5-2 us)
+    if (compact) {
+        int buf = 0;
+        while (chunk < ch_end) {
+            if (chunk + 1 < ch_end) {
+                set_chunk(chunk + 1, std::true_type{});
+                load(buf ^ 1);
+            }
+            compute(buf);
+            wait_vmem();
+            __syncthreads();
+            buf ^= 1;
+            ++chunk;
+        }
+    }
     int buf = 0;
     while (chunk < ch_end) {
         const int next = next_live(chunk + 1);
         if (next < ch_end) {
-            set_chunk(next);
+            set_chunk(next, std::false_type{});
             load(buf ^ 1);
         }
         compute(buf);
@@ -677,7 +781,7 @@ __global__ __launch_bounds__(WTile<BKT>::NT) void bwd_weight_tr_kernel(WeightPar
 
     if (tid == 0) {
         p.skip_slots[blockIdx.x] = skipped;
-        p.work_slots[t] = ch_end - ch_begin - skipped;
+        p.work_slots[t] = ch_end - ch_begin - (compact ? 0 : skipped);
     }
 
     // Buffer stores over this split's [K][RS][C] region: lanes past K, C or

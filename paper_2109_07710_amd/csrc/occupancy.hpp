@@ -46,13 +46,24 @@ __device__ __forceinline__ uint32_t vec_bits(const uint4& v, bool relu)
 // per 64-pixel chunk.
 __device__ __forceinline__ void occupancy_block(const OccParams& p, int block)
 {
-    __shared__ int flags[1024];                  // [chunk of the group][k tile]
+    // Per (chunk of the group, k tile) block a flag, set by the non-zeros it
+    // holds -- or, where the live pixels are recorded (64-pixel chunks, packed
+    // footprint), the block's dead pixels, a bit each: an element-wise
+    // footprint has none and marks nothing.
+    __shared__ uint32_t marks[2048];
+    int* const flags = reinterpret_cast<int*>(marks);
+    uint32_t* const dead_s = marks;
+    const bool pixels = p.pmask != nullptr && p.bits != nullptr;
     const int chunk0 = block * p.cpw;
     const int nloc = min(p.cpw, p.nchunks - chunk0);
     const int px0 = chunk0 * p.chunk;
     const int npx = min(nloc * p.chunk, p.npq - px0);   // pixels of the group
-    for (int i = threadIdx.x; i < nloc * p.ktiles; i += blockDim.x) flags[i] = 0;
+    for (int i = threadIdx.x; i < nloc * p.ktiles * (pixels ? 2 : 1); i += blockDim.x) marks[i] = 0u;
     __syncthreads();
+    auto mark_dead = [&](int i) {   // pair i of the group
+        const int j = (int)fdiv((uint32_t)i, p.div_ktiles), kt = i - j * p.ktiles;
+        atomicOr(&dead_s[2 * ((j >> 6) * p.ktiles + kt) + ((j >> 5) & 1)], 1u << (j & 31));
+    };
     if (p.bits) {
         // whole 8-, 16- or 32-byte aligned word runs per (pixel, k tile) when
         // K is a multiple of the tile width (64, 128 or 256 channels)
@@ -95,11 +106,22 @@ __device__ __forceinline__ void occupancy_block(const OccParams& p, int block)
                         w[u] = (v.x | v.y | v.z | v.w) | (v2.x | v2.y | v2.z | v2.w);
                     }
                 }
+                if (!pixels) {
 #pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    const int key = w[u] != 0u ? idx[u] : -1;
-                    const int prev = __shfl_up(key, 1, 64);
-                    if (key >= 0 && (lane == 0 || prev != key)) flags[idx[u]] = 1;   // every writer stores 1
+                    for (int u = 0; u < 8; ++u) {
+                        const int key = w[u] != 0u ? idx[u] : -1;
+                        const int prev = __shfl_up(key, 1, 64);
+                        if (key >= 0 && (lane == 0 || prev != key)) flags[idx[u]] = 1;   // every writer stores 1
+                    }
+                } else {
+                    uint32_t least = w[0];   // zero iff some pair is dead (or past the group)
+#pragma unroll
+                    for (int u = 1; u < 8; ++u) least = min(least, w[u]);
+                    if (least == 0u) {
+#pragma unroll
+                        for (int u = 0; u < 8; ++u)
+                            if (w[u] == 0u && off[u] != kOOB) mark_dead(i0 + u * blockDim.x);
+                    }
                 }
             }
         };
@@ -111,8 +133,12 @@ __device__ __forceinline__ void occupancy_block(const OccParams& p, int block)
                 const int j = (int)fdiv((uint32_t)i, p.div_ktiles), kt = i - j * p.ktiles;
                 const int64_t base = (int64_t)(px0 + j) * p.K;
                 const int lo = kt * p.BNk, hi = min(p.K, lo + p.BNk);
-                if (any_bits(p.bits, base + lo, base + hi))
+                const bool any = any_bits(p.bits, base + lo, base + hi);
+                if (pixels) {
+                    if (!any) mark_dead(i);
+                } else if (any) {
                     flags[(int)fdiv((uint32_t)j, p.div_chunk) * p.ktiles + kt] = 1;   // every writer stores 1
+                }
             }
         }
     } else {
@@ -131,10 +157,22 @@ __device__ __forceinline__ void occupancy_block(const OccParams& p, int block)
     __syncthreads();
     bool dead = false;
     for (int i = threadIdx.x; i < nloc * p.ktiles; i += blockDim.x) {
-        p.occ[(int64_t)chunk0 * p.ktiles + i] = (uint8_t)(flags[i] != 0);
-        dead |= flags[i] == 0;
+        bool any;
+        if (pixels) {
+            const int cl = (int)fdiv((uint32_t)i, p.div_ktiles), kt = i - cl * p.ktiles;
+            const int left = npx - cl * 64;   // pixels of the block (at least one)
+            const uint64_t valid = left >= 64 ? ~0ull : (1ull << left) - 1;
+            const uint64_t live = valid & ~(((uint64_t)dead_s[2 * i + 1] << 32) | dead_s[2 * i]);
+            p.pmask[(int64_t)kt * p.nchunks + chunk0 + cl] = live;
+            any = live != 0;
+            dead |= 2 * __popcll(live) < __popcll(valid);   // (a dead block among them)
+        } else {
+            any = flags[i] != 0;
+            dead |= !any;
+        }
+        p.occ[(int64_t)chunk0 * p.ktiles + i] = any ? 1 : 0;
     }
-    // the call's dead-block flag (every writer stores the same number)
+    // the call's flag (every writer stores the same number)
     if (__syncthreads_or(dead) && p.any_dead && threadIdx.x == 0) *p.any_dead = (int)p.gen;
 
     // X-window liveness for every (tap group, channel tile) of the weight

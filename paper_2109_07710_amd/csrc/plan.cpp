@@ -355,6 +355,7 @@ int plan_weight(const cbw_conv_desc* d, WeightPlan* out, bool allow_rows)
     size_t cur = 0;
     p.header = take(&cur, 256);
     p.occ = take(&cur, (size_t)p.nchunks * p.ktiles);
+    if (!p.rows && d->dtype == CBW_BF16) p.pmask = take(&cur, (size_t)p.nchunks * p.ktiles * 8);
     p.xlive = take(&cur, (size_t)p.nchunks * p.tgroups * p.ctiles);
     p.xbits = take(&cur, ((size_t)d->N * d->H * d->W * d->C + 31) / 32 * 4);
     p.skip_slots = take(&cur, (size_t)p.grid * 4);

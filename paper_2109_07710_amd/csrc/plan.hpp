@@ -99,7 +99,7 @@ struct WeightPlan {
     int nchunks = 0, ctiles = 0, ktiles = 0, nsplit = 0, chunks_per_split = 0, grid = 0;
     int nparts = 0;         // partials the reduction sums
     bool direct = false;  // partial of the single split is dW itself
-    Region header, occ, xlive, xbits, skip_slots, work_slots, partials;
+    Region header, occ, pmask, xlive, xbits, skip_slots, work_slots, partials;
     // NCHW callers: NHWC copies of X and dY and the NHWC-order dY footprint
     // (a caller's X footprint is reordered into xbits), after every other region
     Region t_x, t_dy, t_dymask;

@@ -1,0 +1,110 @@
+"""GPU parity of the bf16 weight gradient over compacted pixels: dY footprints
+that whole pixels share (most 64-pixel blocks hold a live pixel, few pixels are
+live), against the fp64 oracle and the unskipped run.  The compaction applies
+where the live pixels of a k tile fit half as many blocks as are live; cases
+lie on both sides of that line, with k tiles that differ, ragged last chunks,
+packed taps, strides, every pixel dead, and more live pixels per split than
+the list holds (the chunked path again).
+"""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2109_07710_amd as cb
+from parity import check_dw_regrouped, check_values, tol_for
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # N, C, H, W, K, R, S, stride, pad, share of live pixels per k tile
+    (6, 256, 20, 20, 256, 3, 3, 1, 1, (0.1,)),
+    (6, 256, 20, 20, 256, 3, 3, 1, 1, (0.45,)),        # just under half
+    (6, 256, 20, 20, 256, 3, 3, 1, 1, (0.6,)),         # past half: chunks
+    (5, 136, 17, 19, 520, 3, 3, 1, 1, (0.02, 1.0, 0.3)),   # three k tiles, ragged channels and last chunk
+    (7, 48, 31, 29, 40, 3, 3, 2, 1, (0.2,)),           # packed taps, stride 2, 64-wide k tile
+    (4, 320, 16, 16, 72, 1, 1, 1, 0, (0.01,)),
+    (3, 256, 12, 12, 256, 3, 3, 1, 1, (0.0,)),         # nothing live
+]
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    cb.lib()
+
+
+def _dy(rng, npq, K, shares):
+    dy = rng.standard_normal((npq, K), dtype=np.float32)
+    for i, d in enumerate(shares):
+        dy[rng.random(npq) >= d, i * 256:(i + 1) * 256] = 0.0
+    return dy
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "N%dC%dK%d_%dx%d_f%d_s%d_live%s" % (
+    c[0], c[1], c[4], c[2], c[3], c[5], c[7], "_".join("%g" % d for d in c[9])))
+def test_compacted_weight_gradient(case):
+    N, C, H, W, K, R, S, st, pd, shares = case
+    print("\n[case] compacted dW %s" % (case,), flush=True)
+    rng = np.random.default_rng([210907710, 93, N, C, H, W, K, int(1000 * shares[0])])
+    desc = cb.ConvDesc.make(N, C, H, W, K, R, S, st, (pd, pd))
+    npq = N * desc.P * desc.Q
+    x = torch.from_numpy(np.maximum(rng.standard_normal((N, H, W, C), dtype=np.float32), 0.0)).bfloat16()
+    dy = torch.from_numpy(_dy(rng, npq, K, shares)).bfloat16()
+    xd, dyd = x.cuda(), dy.cuda()
+    bits = torch.zeros(cb.cbw_dy_mask_words(desc), dtype=torch.int32, device="cuda")
+    cb.cbw_nonzero_mask_pack(desc.dtype, dyd.numel(), dyd, bits)
+    ws = cb.workspace(desc, cb.CBW_OP_BWD_WEIGHT)
+    dw = [torch.full((K, R, S, C), float("nan"), device="cuda") for _ in range(3)]
+    cb.conv_bwd_weight_sparse(desc, xd, dyd, bits, dw[0], ws)
+    stats, work = cb.cbw_read_stats(desc, cb.CBW_OP_BWD_WEIGHT, ws), cb.cbw_read_weight_work(desc, ws)
+    occ, chunk, kw = cb.cbw_read_occupancy(desc, ws)
+    cb.conv_bwd_weight_sparse(desc, xd, dyd, bits, dw[1], ws)
+    cb.conv_bwd_weight_sparse(desc, xd, dyd, bits, dw[2], ws, cb.CBW_FLAG_NO_SKIP)
+    torch.cuda.synchronize()
+    assert torch.equal(dw[0].view(torch.int32), dw[1].view(torch.int32))
+    # blocks executed per k tile: the live pixels' own blocks, or the live chunks
+    flat = dy.float().numpy()
+    ref_occ = oracle.block_occupancy(flat, chunk, kw)
+    assert np.array_equal(occ, ref_occ)
+    expect = []
+    for kt in range(ref_occ.shape[1]):
+        blocks = -(-int((flat[:, kt * kw:(kt + 1) * kw] != 0).any(axis=1).sum()) // chunk)
+        live = int(ref_occ[:, kt].sum())
+        expect.append(blocks if 2 * blocks <= live else live)
+    per_tile = work.sum(axis=0)
+    assert np.array_equal(per_tile, np.array([expect[t % len(expect)] for t in range(work.shape[1])]))
+    assert np.array_equal(work.max(axis=0), -(-per_tile // work.shape[0]))
+    assert stats.blocks_skipped == stats.blocks_total - int(per_tile.sum())
+    x64 = oracle.nhwc_to_nchw(x.double().numpy())
+    dy64 = oracle.nhwc_to_nchw(dy.view(N, desc.P, desc.Q, K).double().numpy())
+    ref, ab, nt = oracle.conv_bwd_weight(x64, dy64, (R, S), (st, st), (pd, pd), with_bound=True)
+    check_values(oracle.krsc_to_kcrs(dw[0].cpu().double().numpy()), ref, ab, nt, tol_for("bf16"), False, "compacted dW")
+    check_dw_regrouped(dw[0], dw[2], stats.blocks_skipped, "compacted dW against no skipping")
+
+
+def test_more_live_pixels_than_the_list_holds():
+    """A 1x1 layer whose four channel tiles leave 64 splits: of a million
+    pixels 49% are live, over 7168 per split, so the chunks are walked."""
+    desc = cb.ConvDesc.make(20, 1024, 224, 224, 8, 1, 1)
+    print("\n[case] compacted dW, list too small", flush=True)
+    npq = 20 * 224 * 224
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    x = torch.randn((npq, 1024), generator=g, device="cuda").bfloat16()
+    dy = torch.randn((npq, 8), generator=g, device="cuda")
+    dy[torch.rand(npq, generator=g, device="cuda") >= 0.49] = 0.0
+    dy = dy.bfloat16()
+    bits = torch.zeros(cb.cbw_dy_mask_words(desc), dtype=torch.int32, device="cuda")
+    cb.cbw_nonzero_mask_pack(desc.dtype, dy.numel(), dy, bits)
+    ws = cb.workspace(desc, cb.CBW_OP_BWD_WEIGHT)
+    a, b = (torch.empty((8, 1, 1, 1024), device="cuda") for _ in range(2))
+    cb.conv_bwd_weight_sparse(desc, x, dy, bits, a, ws)
+    st = cb.cbw_read_stats(desc, cb.CBW_OP_BWD_WEIGHT, ws)
+    cb.conv_bwd_weight_sparse(desc, x, dy, bits, b, ws, cb.CBW_FLAG_NO_SKIP)
+    live = (dy != 0).any(dim=1).sum().item()
+    nsplit = cb.cbw_read_weight_work(desc, ws).shape[0]
+    assert -(-(-(-live // 64)) // nsplit) * 64 > 7168, "the case has to exceed the list"
+    assert st.blocks_skipped == 0
+    assert torch.equal(a, b)
