@@ -774,9 +774,7 @@ static int run_bwd_both(const cbw_conv_desc* desc, const void* X, const void* dY
         // tiling) keeps a launch of its own.
         if ((e = launch_bwd_weight(desc->dtype, wp, s, prof_events(1))) != hipSuccess) return hip_status(e);
         dp.dw_red = rp;
-        if ((e = launch_bwd_data(desc->dtype, mode, dp, s, prof_events(0), false)) != hipSuccess) return hip_status(e);
-        const bool dx_reduce = mode == MODE_GATHER || dplan.split > 1;
-        return finish(dx_reduce ? launch_bwd_reduce(desc->dtype, mode, dp, true, ReduceParams{}, s) : hipSuccess);
+        return finish(launch_bwd_data(desc->dtype, mode, dp, s, prof_events(0)));
     }
     if (dplan.rows) {
         const DataRowsParams rwp = data_rows_params(desc, dplan, dY, wt, x_mask, dX, ws, skip);
@@ -787,7 +785,9 @@ static int run_bwd_both(const cbw_conv_desc* desc, const void* X, const void* dY
     }
     if (e != hipSuccess) return hip_status(e);
     if ((e = launch_bwd_weight(desc->dtype, wp, s, prof_events(1))) != hipSuccess) return hip_status(e);
-    return finish(launch_bwd_reduce(desc->dtype, mode, dp, false, rp, s));
+    if (rp.blocks > 0)
+        e = launch_splitk_reduce(rp.part, rp.dw, rp.nsplit, rp.K, rp.RS, rp.C, rp.krsc, s);
+    return finish(e);
 }
 
 int conv_bwd_data_elementwise(const cbw_conv_desc* desc, const void* dY, const void* W, const uint32_t* x_mask,

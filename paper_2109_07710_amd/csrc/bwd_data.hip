@@ -1142,41 +1142,6 @@ int data_reduce_blocks(const DataParams& p)
     return (int)std::max<int64_t>(p.nslots, (nvec + 255) / 256);
 }
 
-// The split reductions of both gradients in one launch (the call that
-// computes both): blocks [0, dw_blocks) sum the weight gradient's split-K
-// partials (G threads per output), the next dx_blocks blocks the data
-// gradient's split tiles (when its reduction was split; they exit at once
-// otherwise).
-template <typename T, bool UNIT>
-__global__ __launch_bounds__(256) void bwd_reduce_kernel(ParamsFor<UNIT> dp, int dx_mode, int dx_blocks, ReduceParams rp)
-{
-    const int b = blockIdx.x;
-    if (b < rp.blocks) {
-        switch (rp.G) {
-        case 1: splitk_reduce_block<1>(rp.part, rp.dw, rp.nsplit, rp.K, rp.RS, rp.C, rp.krsc, b); break;
-        case 2: splitk_reduce_block<2>(rp.part, rp.dw, rp.nsplit, rp.K, rp.RS, rp.C, rp.krsc, b); break;
-        case 4: splitk_reduce_block<4>(rp.part, rp.dw, rp.nsplit, rp.K, rp.RS, rp.C, rp.krsc, b); break;
-        case 8: splitk_reduce_block<8>(rp.part, rp.dw, rp.nsplit, rp.K, rp.RS, rp.C, rp.krsc, b); break;
-        default: splitk_reduce_block<16>(rp.part, rp.dw, rp.nsplit, rp.K, rp.RS, rp.C, rp.krsc, b); break;
-        }
-        return;
-    }
-    const int db = b - rp.blocks;
-    if (dx_mode == MODE_GATHER) {
-        if (dp.tile == 0) data_reduce_block<T, MODE_GATHER, 0, UNIT>(dp, db, dx_blocks);
-        else if (dp.tile == 1) data_reduce_block<T, MODE_GATHER, 1, UNIT>(dp, db, dx_blocks);
-        else data_reduce_block<T, MODE_GATHER, 2, UNIT>(dp, db, dx_blocks);
-    } else if (dx_mode == MODE_SELECT) {
-        if (dp.tile == 0) data_reduce_block<T, MODE_SELECT, 0, UNIT>(dp, db, dx_blocks);
-        else if (dp.tile == 1) data_reduce_block<T, MODE_SELECT, 1, UNIT>(dp, db, dx_blocks);
-        else data_reduce_block<T, MODE_SELECT, 2, UNIT>(dp, db, dx_blocks);
-    } else {
-        if (dp.tile == 0) data_reduce_block<T, MODE_DENSE, 0, UNIT>(dp, db, dx_blocks);
-        else if (dp.tile == 1) data_reduce_block<T, MODE_DENSE, 1, UNIT>(dp, db, dx_blocks);
-        else data_reduce_block<T, MODE_DENSE, 2, UNIT>(dp, db, dx_blocks);
-    }
-}
-
 }  // namespace
 
 int data_tile_channels(int tile)
@@ -1217,21 +1182,6 @@ hipError_t launch_data_prep(int dtype, const void* w, void* wt, int K, int C, in
     return hipGetLastError();
 }
 
-hipError_t launch_bwd_reduce(int dtype, int dx_mode, const DataParamsStrided& dp, bool dx_reduce, const ReduceParams& rp,
-                             hipStream_t stream)
-{
-    const int dx_blocks = dx_reduce ? data_reduce_blocks(dp) : 0;
-    const int nb = rp.blocks + dx_blocks;
-    if (nb == 0) return hipSuccess;
-    if (dx_reduce && (dp.tile < 0 || dp.tile >= kDataTileCount || dp.smax > kMaxDataSplit)) return hipErrorInvalidValue;
-    const bool unit = dp.ncls == 0;
-    if (dtype == 1 && unit) bwd_reduce_kernel<uint16_t, true><<<nb, 256, 0, stream>>>(dp, dx_mode, dx_blocks, rp);
-    else if (dtype == 1) bwd_reduce_kernel<uint16_t, false><<<nb, 256, 0, stream>>>(dp, dx_mode, dx_blocks, rp);
-    else if (unit) bwd_reduce_kernel<float, true><<<nb, 256, 0, stream>>>(dp, dx_mode, dx_blocks, rp);
-    else bwd_reduce_kernel<float, false><<<nb, 256, 0, stream>>>(dp, dx_mode, dx_blocks, rp);
-    return hipGetLastError();
-}
-
 hipError_t launch_fwd_prep(int dtype, const void* w, void* wt, int K, int C, int R, int S, int krsc, int* header,
                            uint32_t* zero, int64_t zero_words, hipStream_t stream)
 {
@@ -1254,13 +1204,13 @@ namespace {
 // GEMM (and, when the reduction may be split, the partial-tile reduction) of
 // one element type, mode and tile shape.
 template <typename T, int MODE, int TI, bool UNIT>
-hipError_t launch_strides(const ParamsFor<UNIT>& p, int nb, hipStream_t stream, const ProfEvents& ev, bool with_reduce)
+hipError_t launch_strides(const ParamsFor<UNIT>& p, int nb, hipStream_t stream, const ProfEvents& ev)
 {
     hipError_t e =
         launch_timed(bwd_data_kernel<T, MODE, UNIT, TI>, dim3(nb), dim3(Tile<TI>::NT), stream, ev, p);
     if (e != hipSuccess) return e;
     // in gather mode the split is only known on the device
-    if (with_reduce && (MODE == MODE_GATHER || p.split > 1)) {
+    if (MODE == MODE_GATHER || p.split > 1) {
         splitk_data_reduce_kernel<T, MODE, TI, UNIT><<<data_reduce_blocks(p), 256, 0, stream>>>(p);
         e = hipGetLastError();
     }
@@ -1268,34 +1218,33 @@ hipError_t launch_strides(const ParamsFor<UNIT>& p, int nb, hipStream_t stream, 
 }
 
 template <typename T, int MODE, int TI>
-hipError_t launch_shape(const DataParamsStrided& p, int nb, hipStream_t stream, const ProfEvents& ev, bool wr)
+hipError_t launch_shape(const DataParamsStrided& p, int nb, hipStream_t stream, const ProfEvents& ev)
 {
-    if (p.stride_h == 1 && p.stride_w == 1) return launch_strides<T, MODE, TI, true>(p, nb, stream, ev, wr);
+    if (p.stride_h == 1 && p.stride_w == 1) return launch_strides<T, MODE, TI, true>(p, nb, stream, ev);
     if constexpr (MODE == MODE_FWD) return hipErrorInvalidValue;   // the forward runs stride 1 only
-    else return launch_strides<T, MODE, TI, false>(p, nb, stream, ev, wr);
+    else return launch_strides<T, MODE, TI, false>(p, nb, stream, ev);
 }
 
 template <typename T, int MODE>
-hipError_t launch_mode(const DataParamsStrided& p, int nb, hipStream_t stream, const ProfEvents& ev, bool wr)
+hipError_t launch_mode(const DataParamsStrided& p, int nb, hipStream_t stream, const ProfEvents& ev)
 {
-    if (p.tile == 0) return launch_shape<T, MODE, 0>(p, nb, stream, ev, wr);
-    if (p.tile == 1) return launch_shape<T, MODE, 1>(p, nb, stream, ev, wr);
-    return launch_shape<T, MODE, 2>(p, nb, stream, ev, wr);
+    if (p.tile == 0) return launch_shape<T, MODE, 0>(p, nb, stream, ev);
+    if (p.tile == 1) return launch_shape<T, MODE, 1>(p, nb, stream, ev);
+    return launch_shape<T, MODE, 2>(p, nb, stream, ev);
 }
 
 template <typename T>
-hipError_t launch_type(int mode, const DataParamsStrided& p, int nb, hipStream_t stream, const ProfEvents& ev, bool wr)
+hipError_t launch_type(int mode, const DataParamsStrided& p, int nb, hipStream_t stream, const ProfEvents& ev)
 {
-    if (mode == MODE_DENSE) return launch_mode<T, MODE_DENSE>(p, nb, stream, ev, wr);
-    if (mode == MODE_SELECT) return launch_mode<T, MODE_SELECT>(p, nb, stream, ev, wr);
-    if (mode == MODE_FWD) return launch_mode<T, MODE_FWD>(p, nb, stream, ev, wr);
-    return launch_mode<T, MODE_GATHER>(p, nb, stream, ev, wr);
+    if (mode == MODE_DENSE) return launch_mode<T, MODE_DENSE>(p, nb, stream, ev);
+    if (mode == MODE_SELECT) return launch_mode<T, MODE_SELECT>(p, nb, stream, ev);
+    if (mode == MODE_FWD) return launch_mode<T, MODE_FWD>(p, nb, stream, ev);
+    return launch_mode<T, MODE_GATHER>(p, nb, stream, ev);
 }
 
 }  // namespace
 
-hipError_t launch_bwd_data(int dtype, int mode, const DataParamsStrided& p, hipStream_t stream, const ProfEvents& ev,
-                           bool with_reduce)
+hipError_t launch_bwd_data(int dtype, int mode, const DataParamsStrided& p, hipStream_t stream, const ProfEvents& ev)
 {
     // enough workgroups for every tile of the dense tiling unsplit, or for
     // nslots split items.  Gather mode fits too: with at most as many live
@@ -1317,8 +1266,8 @@ hipError_t launch_bwd_data(int dtype, int mode, const DataParamsStrided& p, hipS
             return hipErrorInvalidValue;
         tail = (r.blocks + 3) / 4;
     }
-    return dtype == 1 ? launch_type<uint16_t>(mode, q, nb + tail, stream, ev, with_reduce)
-                      : launch_type<float>(mode, q, nb + tail, stream, ev, with_reduce);
+    return dtype == 1 ? launch_type<uint16_t>(mode, q, nb + tail, stream, ev)
+                      : launch_type<float>(mode, q, nb + tail, stream, ev);
 }
 
 }  // namespace cbw

@@ -229,14 +229,9 @@ int compact_block_pixels();
 // occupancy) in one launch.
 hipError_t launch_data_prep(int dtype, const void* w, void* wt, int K, int C, int RS, int krsc, int* header,
                             int mode, const CompactParams* cp, hipStream_t stream, const OccParams* op = nullptr);
-// with_reduce = false leaves a split reduction to launch_bwd_reduce.
-hipError_t launch_bwd_data(int dtype, int mode, const DataParamsStrided& p, hipStream_t stream, const ProfEvents& ev,
-                           bool with_reduce = true);
-// The weight gradient's split-K reduction (rp.blocks workgroups, none when
-// dW was written directly) and, when dx_reduce, the data gradient's split
-// tiles, in one launch.
-hipError_t launch_bwd_reduce(int dtype, int dx_mode, const DataParamsStrided& dp, bool dx_reduce, const ReduceParams& rp,
-                             hipStream_t stream);
+// The data-gradient GEMM and, when its reduction may be split, the launch
+// that sums the partial tiles.
+hipError_t launch_bwd_data(int dtype, int mode, const DataParamsStrided& p, hipStream_t stream, const ProfEvents& ev);
 // Forward preparation: Wf[tap'][k][c] = W[k][tap][c] with tap' the flipped tap
 // (R-1-r, S-1-s), the workspace header stamped, and `zero_words` words of
 // `zero` cleared (footprint words filled by atomic OR), in one launch.
