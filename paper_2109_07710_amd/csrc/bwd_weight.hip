@@ -197,8 +197,8 @@ __device__ bool split_range(const WeightParams& p, int kt, int combo, int z, int
 // belongs to block r / 64, and split z takes ceil(blocks / nsplit) of them in
 // order, its pixels listed in list[] (npq, past the last pixel, fills the
 // last block: it reads zeros).  Products left out are exactly zero.  Half is
-// well past the break-even: listing costs a few microseconds a launch, a
-// block about 1.3 us.  Called by the whole workgroup; scratch as in
+// well past the break-even, and every split has to save four blocks on
+// average: listing costs a few microseconds a launch, a block about 1.3 us.  Called by the whole workgroup; scratch as in
 // split_range.  False (nothing changed): not worth it, or more pixels per
 // split than list[] holds.  512 channels, 14 x 14, N = 128, 10% of the
 // pixels live in every channel: 100 us for 81% of the blocks, 31 us here.
@@ -240,7 +240,7 @@ __device__ bool compact_range(const WeightParams& p, int kt, int combo, int z, i
     total = __builtin_amdgcn_readfirstlane(total);
     live = __builtin_amdgcn_readfirstlane(live);
     const int blocks = (total + TR_BK - 1) / TR_BK, share = (blocks + p.nsplit - 1) / p.nsplit;
-    if (2 * blocks > live || share * TR_BK > LIST_CAP) {
+    if (2 * blocks > live || live - blocks < kCompactMinSaved * p.nsplit || share * TR_BK > LIST_CAP) {
         __syncthreads();   // the scratch is free again
         return false;
     }
@@ -722,23 +722,29 @@ __global__ __launch_bounds__(WTile<BKT>::NT) void bwd_weight_tr_kernel(WeightPar
         load(0);
     }
     uint32_t dflag = 0;
-    if (p.occ) dflag = __builtin_amdgcn_raw_buffer_load_b32(make_rsrc(p.header, 64), 4 * kDeadWord, 0, 0);
+    uint32_t cflag = 0;
+    if (p.occ) {
+        dflag = __builtin_amdgcn_raw_buffer_load_b32(make_rsrc(p.header, 64), 4 * kDeadWord, 0, 0);
+        cflag = __builtin_amdgcn_raw_buffer_load_b32(make_rsrc(p.header, 64), 4 * kDeadWord + 4, 0, 0);
+    }
     wait_vmem();
     __syncthreads();
     bool all_live = true;
     int skipped = 0;
-    if (p.occ && __builtin_amdgcn_readfirstlane(dflag) == p.gen) {
-        if (p.pmask) {
+    const bool any_dead = __builtin_amdgcn_readfirstlane(dflag) == p.gen;
+    const bool sparse = p.pmask && __builtin_amdgcn_readfirstlane(cflag) == p.gen;
+    if (p.occ && (any_dead || sparse)) {
+        if (sparse) {
             int nblocks = 0;
             compact = compact_range(p, kt, combo, z, ch_begin, ch_end, nblocks, list_s,
                                     reinterpret_cast<uint8_t*>(As[1]));
             list0 = ch_begin;
             if (compact && z == 0) skipped = p.nchunks - nblocks;   // (the splits' sum: blocks not executed)
         }
-        if (!compact)
+        if (!compact && any_dead)
             all_live = split_range(p, kt, combo, z, ch_begin, ch_end, live_s, reinterpret_cast<uint8_t*>(As[1]));
         chunk = all_live ? ch_begin : next_live_chunk(p, live_s, ch_begin, ch_end, kt, combo, ch_begin, skipped);
-        if (chunk < ch_end) {
+        if (chunk < ch_end && (compact || any_dead)) {
             if (compact) set_chunk(chunk, std::true_type{});
             else set_chunk(chunk, std::false_type{});
             load(0);

@@ -174,7 +174,7 @@ struct WeightParams {
     uint32_t gen;
     const uint64_t* pmask;   // [ktiles][nchunks] live pixels of each block, or null (see OccParams)
 };
-constexpr int kDeadWord = 4;   // weight workspace header word of the dead-block flag
+constexpr int kDeadWord = 4;   // weight workspace header words: the dead-block flag, then the compaction flag
 
 struct OccParams {
     const void* dy;          // values [npq][K] (used when bits == null)
@@ -191,10 +191,11 @@ struct OccParams {
     int tpg, tgroups, ctiles, ctw;   // taps per group, groups, channel tiles, channels per tile
     FastDiv div_q, div_p;
     FastDiv div_chunk, div_ktiles;   // pixel -> chunk, pair -> pixel
-    // The call's flag: a workgroup that finds a dead block (or a dead X
-    // window; with pmask also a block with more dead pixels than live ones)
-    // stores gen, this call's number, into *any_dead, which the GEMM
-    // compares with the same number (nullable).
+    // The call's flags: a workgroup that finds a dead block (or a dead X
+    // window) stores gen, this call's number, into any_dead[0], and with
+    // pmask one whose live pixels of some k tile fit half its live blocks
+    // into any_dead[1]; the GEMM compares them with the same number
+    // (nullable).
     int* any_dead;
     // live pixels of every (k tile, 64-pixel chunk), a bit each (nullable;
     // written when dY's packed footprint is given)

@@ -51,6 +51,8 @@ __device__ __forceinline__ void occupancy_block(const OccParams& p, int block)
     // footprint), the block's dead pixels, a bit each: an element-wise
     // footprint has none and marks nothing.
     __shared__ uint32_t marks[2048];
+    __shared__ int found_s;                      // 1: a dead block, 2: one with more dead pixels than live ones
+    if (threadIdx.x == 0) found_s = 0;
     int* const flags = reinterpret_cast<int*>(marks);
     uint32_t* const dead_s = marks;
     const bool pixels = p.pmask != nullptr && p.bits != nullptr;
@@ -155,7 +157,7 @@ __device__ __forceinline__ void occupancy_block(const OccParams& p, int block)
         }
     }
     __syncthreads();
-    bool dead = false;
+    bool dead = false, sparse = false;
     for (int i = threadIdx.x; i < nloc * p.ktiles; i += blockDim.x) {
         bool any;
         if (pixels) {
@@ -165,15 +167,37 @@ __device__ __forceinline__ void occupancy_block(const OccParams& p, int block)
             const uint64_t live = valid & ~(((uint64_t)dead_s[2 * i + 1] << 32) | dead_s[2 * i]);
             p.pmask[(int64_t)kt * p.nchunks + chunk0 + cl] = live;
             any = live != 0;
-            dead |= 2 * __popcll(live) < __popcll(valid);   // (a dead block among them)
+            sparse |= any && 2 * __popcll(live) <= 64;
         } else {
             any = flags[i] != 0;
-            dead |= !any;
         }
+        dead |= !any;
         p.occ[(int64_t)chunk0 * p.ktiles + i] = any ? 1 : 0;
     }
-    // the call's flag (every writer stores the same number)
-    if (__syncthreads_or(dead) && p.any_dead && threadIdx.x == 0) *p.any_dead = (int)p.gen;
+    // the call's flags (every writer stores the same number)
+    if (dead || sparse) atomicOr(&found_s, (dead ? 1 : 0) | (sparse ? 2 : 0));
+    __syncthreads();
+    const int found = found_s;
+    if ((found & 1) && p.any_dead && threadIdx.x == 0) p.any_dead[0] = (int)p.gen;
+    if ((found & 2) && p.any_dead) {
+        // A k tile whose live pixels fit half its live blocks has a workgroup
+        // where they do, so the GEMM's count over the whole tile (two passes
+        // of its ranking, 4 us) runs only if one says so: footprints of
+        // clustered pixels have sparse blocks at densities where nothing can
+        // be gained.  Per k tile the sum of 2 live - 64 over the live blocks,
+        // scaled so that a sum of zero with a live block counts.
+        __shared__ int sum[1024];
+        for (int i = threadIdx.x; i < p.ktiles; i += blockDim.x) sum[i] = 0;
+        __syncthreads();
+        for (int i = threadIdx.x; i < nloc * p.ktiles; i += blockDim.x) {
+            const int cl = (int)fdiv((uint32_t)i, p.div_ktiles);
+            const int n = min(64, npx - cl * 64) - __popc(dead_s[2 * i]) - __popc(dead_s[2 * i + 1]);
+            if (n > 0) atomicAdd(&sum[i - cl * p.ktiles], 2048 * (2 * n - 64) - 1);
+        }
+        __syncthreads();
+        for (int i = threadIdx.x; i < p.ktiles; i += blockDim.x)
+            if (sum[i] < 0) p.any_dead[1] = (int)p.gen;
+    }
 
     // X-window liveness for every (tap group, channel tile) of the weight
     // gradient's tiling: 1 iff some pixel of the chunk has, at one of the

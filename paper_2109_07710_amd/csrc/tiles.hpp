@@ -30,6 +30,9 @@ constexpr int kDataTileCount = 3;
 // Pixel classes (stride_h * stride_w of them) the strided data gradient
 // separates; larger strides walk every tap of every pixel.
 constexpr int kDataMaxClasses = 16;
+// Chunks per split from which the bf16 weight gradient may compact dY's live
+// pixels, and the blocks per split it has to save.
+constexpr int kCompactMinChunks = 16, kCompactMinSaved = 4;
 // Compaction groups (channel tiles) the gather mode handles; wider layers
 // run the masked data gradient without compaction (footprint select only).
 constexpr int kGatherMaxGroups = 16;

@@ -1,8 +1,9 @@
 """GPU parity of the bf16 weight gradient over compacted pixels: dY footprints
 that whole pixels share (most 64-pixel blocks hold a live pixel, few pixels are
 live), against the fp64 oracle and the unskipped run.  The compaction applies
-where the live pixels of a k tile fit half as many blocks as are live; cases
-lie on both sides of that line, with k tiles that differ, ragged last chunks,
+where a split has sixteen chunks or more, the live pixels of a k tile fit half
+as many blocks as are live and every split saves four of them on average;
+cases lie on both sides of these lines, with k tiles that differ, ragged last chunks,
 packed taps, strides, every pixel dead, and more live pixels per split than
 the list holds (the chunked path again).
 """
@@ -18,13 +19,21 @@ pytestmark = pytest.mark.gpu
 
 CASES = [
     # N, C, H, W, K, R, S, stride, pad, share of live pixels per k tile
+    (36, 256, 20, 20, 512, 3, 3, 1, 1, (0.1, 0.1)),        # 17 chunks a split
+    (36, 256, 20, 20, 512, 3, 3, 1, 1, (0.45, 0.02)),      # just under half, and few
+    (36, 256, 20, 20, 512, 3, 3, 1, 1, (0.6, 0.6)),        # past half: chunks
+    (30, 136, 17, 19, 520, 3, 3, 1, 1, (0.02, 1.0, 0.3)),  # three k tiles, ragged channels and last chunk
+    (550, 48, 31, 29, 40, 3, 3, 2, 1, (0.2,)),             # packed taps, stride 2, 64-wide k tile
+    (520, 320, 16, 16, 72, 1, 1, 1, 0, (0.01,)),
+    (200, 256, 12, 12, 256, 3, 3, 1, 1, (0.0,)),           # nothing live
+    # few chunks a split: live pixels are not recorded, live chunks are walked
     (6, 256, 20, 20, 256, 3, 3, 1, 1, (0.1,)),
-    (6, 256, 20, 20, 256, 3, 3, 1, 1, (0.45,)),        # just under half
-    (6, 256, 20, 20, 256, 3, 3, 1, 1, (0.6,)),         # past half: chunks
-    (5, 136, 17, 19, 520, 3, 3, 1, 1, (0.02, 1.0, 0.3)),   # three k tiles, ragged channels and last chunk
+    (6, 256, 20, 20, 256, 3, 3, 1, 1, (0.45,)),
+    (6, 256, 20, 20, 256, 3, 3, 1, 1, (0.6,)),
+    (5, 136, 17, 19, 520, 3, 3, 1, 1, (0.02, 1.0, 0.3)),
     (7, 48, 31, 29, 40, 3, 3, 2, 1, (0.2,)),           # packed taps, stride 2, 64-wide k tile
     (4, 320, 16, 16, 72, 1, 1, 1, 0, (0.01,)),
-    (3, 256, 12, 12, 256, 3, 3, 1, 1, (0.0,)),         # nothing live
+    (3, 256, 12, 12, 256, 3, 3, 1, 1, (0.0,)),
 ]
 
 
@@ -72,7 +81,9 @@ def test_compacted_weight_gradient(case):
     for kt in range(ref_occ.shape[1]):
         blocks = -(-int((flat[:, kt * kw:(kt + 1) * kw] != 0).any(axis=1).sum()) // chunk)
         live = int(ref_occ[:, kt].sum())
-        expect.append(blocks if 2 * blocks <= live else live)
+        long = -(-ref_occ.shape[0] // work.shape[0]) >= 16
+        saves = 2 * blocks <= live and live - blocks >= 4 * work.shape[0]
+        expect.append(blocks if long and saves else live)
     per_tile = work.sum(axis=0)
     assert np.array_equal(per_tile, np.array([expect[t % len(expect)] for t in range(work.shape[1])]))
     assert np.array_equal(work.max(axis=0), -(-per_tile // work.shape[0]))
