@@ -96,8 +96,10 @@ struct DataParams {
 // The same with the pixel classes, for strides above 1 (a type of its own:
 // carrying a kilobyte of classes through every launch cost the unit-stride
 // split reduction 3 us).
+constexpr int kDataTileSteps = 8;   // what starting and finishing a tile costs, in steps
 struct DataParamsStrided : DataParams {
     int ncls;                // 0: every tap of every pixel
+    int64_t cls_cost;        // steps of the class tiling, a tile counted kDataTileSteps on top
     DataClass cls[kDataMaxClasses];   // most taps first
 };
 

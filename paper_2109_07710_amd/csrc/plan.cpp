@@ -212,7 +212,10 @@ int plan_data(const cbw_conv_desc* d, bool masked, DataPlan* out, bool no_split,
     }
     const int bk = 8 * (d->dtype == CBW_BF16 ? 8 : 4);
     p.nsteps = d->R * d->S * ((d->K + bk - 1) / bk);
-    p.split = no_split ? 1 : host_data_split(p.ptiles * p.groups, p.nsteps);
+    // (classes: no finer than the longest one's steps, the rest would write
+    // partials for nothing)
+    const int split_steps = p.ncls > 0 ? std::max(1, p.cls[0].nr * p.cls[0].ns * (p.nsteps / (d->R * d->S))) : p.nsteps;
+    p.split = no_split ? 1 : host_data_split(p.ptiles * p.groups, split_steps);
     p.header = take(&cur, 256);
     p.wt = take(&cur, (size_t)d->K * d->C * d->R * d->S * elem_bytes(d->dtype));
     if (masked) {

@@ -38,7 +38,7 @@ def _gpu():
     cb.lib()
 
 
-@pytest.mark.parametrize("dead", [False, True], ids=["live", "dead_pixels"])
+@pytest.mark.parametrize("dead", [False, True, "few", "most"], ids=["live", "dead_pixels", "few_dead", "most_dead"])
 @pytest.mark.parametrize("case", CASES, ids=lambda c: "%s_N%dC%dK%d_%dx%d_f%dx%d_s%dx%d" % (
     c[9], c[0], c[1], c[4], c[2], c[3], c[5], c[6], *c[7]))
 def test_strided_dx(case, dead):
@@ -49,7 +49,7 @@ def test_strided_dx(case, dead):
     desc = cb.ConvDesc.make(N, C, H, W, K, R, S, st, pd, dtype=dt)
     x = np.maximum(rng.standard_normal((N, H, W, C), dtype=np.float32), 0.0)
     if dead:
-        x[rng.random((N, H, W)) < 0.5] = 0.0
+        x[rng.random((N, H, W)) < {True: 0.5, "few": 0.01, "most": 0.9}[dead]] = 0.0
     else:
         x[..., 0] += 0.5
     x = torch.from_numpy(x).to(td)
@@ -62,7 +62,11 @@ def test_strided_dx(case, dead):
     cb.conv_bwd_data(desc, dy.cuda(), w.cuda(), dx["dense"], ws)
     cb.conv_bwd_data_masked(desc, dy.cuda(), w.cuda(), xm, dx["select"], ws, cb.CBW_FLAG_NO_SKIP)
     cb.conv_bwd_data_masked(desc, dy.cuda(), w.cuda(), xm, dx["masked"], ws)
+    lists = [cb.cbw_read_live_lists(desc, ws, g) for g in range(-(-C // cb.cbw_read_live_lists(desc, ws, 0)[1]))]
     torch.cuda.synchronize()
+    for g, (got, width) in enumerate(lists):
+        live = (x[..., g * width:(g + 1) * width] > 0).any(dim=3).flatten().nonzero().flatten()
+        assert np.array_equal(np.asarray(got), live.numpy())
     dy64 = oracle.nhwc_to_nchw(dy.double().numpy())
     w64 = oracle.krsc_to_kcrs(w.double().numpy())
     ref, ab, nt = oracle.conv_bwd_data(dy64, w64, (H, W), st, pd, with_bound=True)
