@@ -102,7 +102,7 @@ void data_gemm_params(const cbw_conv_desc* desc, const DataPlan& plan, const voi
         p.cls[c] = DataClass{k.tile0, (int)k.npix, k.nh, k.nw, k.i0, k.j0, k.a, k.b, k.nr, k.ns,
                              make_fastdiv((uint32_t)k.nw), make_fastdiv((uint32_t)k.nh)};
         const int64_t tiles = (k.npix + plan.brows - 1) / plan.brows;
-        p.cls_cost += tiles * (k.nr * k.ns * (plan.nsteps / (desc->R * desc->S)) + kDataTileSteps);
+        p.cls_cost += tiles * plan.groups * (k.nr * k.ns * (plan.nsteps / (desc->R * desc->S)) + kDataTileSteps);
     }
     p.partial = plan.partial.bytes ? at<float>(ws, plan.partial) : nullptr;
     CompactParams cp{};

@@ -262,15 +262,13 @@ __device__ __forceinline__ int class_pixel(const DataParamsStrided& p, const Dat
 
 // Gather mode with dead pixels: whether the class tiling over all pixels is
 // cheaper than the live lists, which walk every tap of each of their pixels,
-// by the steps of both (n tiles, a live total per group).  Element-wise
+// by the steps of both (`listed` tiles of the lists).  Element-wise
 // footprints of narrow layers have a few dead pixels: 8 -> 280 channels,
 // 3x3 stride 2, 199x199, N = 3, 64% of the elements live: both gradients
 // 94.6 us over the lists, 74.8 over the classes.
-__device__ __forceinline__ bool classes_win(const DataParamsStrided& p, const int* live, int bn, int nsteps)
+__device__ __forceinline__ bool classes_win(const DataParamsStrided& p, int listed, int nsteps)
 {
-    int64_t n = 0;
-    for (int g = 0; g < p.ctiles; ++g) n += (live[g] + bn - 1) / bn;
-    return p.ncls > 0 && n * (nsteps + kDataTileSteps) > p.cls_cost * p.ctiles;
+    return p.ncls > 0 && (int64_t)listed * (nsteps + kDataTileSteps) > p.cls_cost;
 }
 
 template <bool UNIT>
@@ -701,7 +699,9 @@ __global__ __launch_bounds__(Tile<TI>::NT) void bwd_data_kernel(ParamsFor<UNIT> 
         bool all = true;
         for (int g = 0; g < p.ctiles; ++g) all &= gtot_s[g] == p.npix;
         if constexpr (MODE == MODE_GATHER && !UNIT) {
-            relist = !all && classes_win(p, gtot_s, BN, nsteps);
+            int tiles = 0;
+            for (int g = 0; g < p.ctiles; ++g) tiles += (gtot_s[g] + BN - 1) / BN;
+            relist = !all && classes_win(p, tiles, nsteps);
             all |= relist;
         }
         map_item(__builtin_amdgcn_readfirstlane((int)all) != 0);
@@ -1051,7 +1051,7 @@ __device__ __forceinline__ void data_reduce_block(const ParamsFor<UNIT>& p, int 
             ntiles += (p.counts[g] + BN - 1) / BN;
             all &= p.counts[g] == p.npix;
         }
-        if constexpr (!UNIT) all = all || classes_win(p, p.counts, BN, nsteps);
+        if constexpr (!UNIT) all = all || classes_win(p, ntiles, nsteps);
         if (all) ntiles = p.ptiles * p.ctiles;   // the dense tiling
         nsplit = all ? p.split : data_split(ntiles, nsteps, p.nslots, p.smax);
         dense_map = all;

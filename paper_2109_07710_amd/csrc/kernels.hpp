@@ -99,7 +99,7 @@ struct DataParams {
 constexpr int kDataTileSteps = 8;   // what starting and finishing a tile costs, in steps
 struct DataParamsStrided : DataParams {
     int ncls;                // 0: every tap of every pixel
-    int64_t cls_cost;        // steps of the class tiling, a tile counted kDataTileSteps on top
+    int64_t cls_cost;        // steps of the class tiling, every tile kDataTileSteps on top
     DataClass cls[kDataMaxClasses];   // most taps first
 };
 
