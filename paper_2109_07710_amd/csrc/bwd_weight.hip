@@ -202,7 +202,7 @@ __device__ bool split_range(const WeightParams& p, int kt, int combo, int z, int
 // split_range.  False (nothing changed): not worth it, or more pixels per
 // split than list[] holds.  512 channels, 14 x 14, N = 128, 10% of the
 // pixels live in every channel: 100 us for 81% of the blocks, 31 us here.
-constexpr int LIST_CAP = 7168;
+static_assert(kCompactPixels == TR_BK, "a compacted block is a step of the main loop");
 __device__ bool compact_range(const WeightParams& p, int kt, int combo, int z, int& begin, int& end, int& nblocks,
                               int* list, uint8_t* scratch)
 {
@@ -239,15 +239,16 @@ __device__ bool compact_range(const WeightParams& p, int kt, int combo, int z, i
     }
     total = __builtin_amdgcn_readfirstlane(total);
     live = __builtin_amdgcn_readfirstlane(live);
-    const int blocks = (total + TR_BK - 1) / TR_BK, share = (blocks + p.nsplit - 1) / p.nsplit;
-    if (2 * blocks > live || live - blocks < kCompactMinSaved * p.nsplit || share * TR_BK > LIST_CAP) {
+    const CompactShare cs = compact_share(total, p.nsplit, z);
+    const int blocks = cs.blocks;
+    if (2 * blocks > live || live - blocks < kCompactMinSaved * p.nsplit || cs.share * TR_BK > kCompactListCap) {
         __syncthreads();   // the scratch is free again
         return false;
     }
-    begin = min(z * share, blocks);
-    end = min(begin + share, blocks);
+    begin = cs.begin;
+    end = cs.end;
     nblocks = blocks;
-    const int r0 = begin * TR_BK, r1 = min(end * TR_BK, total);
+    const int r0 = cs.first, r1 = cs.last;
     for (int i = r1 - r0 + tid; i < (end - begin) * TR_BK; i += T) list[i] = p.npq;
     int rank = incl - cnt;
     for (int c = s0; c < s1 && rank < r1; ++c) {
@@ -574,7 +575,7 @@ __global__ __launch_bounds__(WTile<BKT>::NT) void bwd_weight_tr_kernel(WeightPar
     constexpr int TM = WTile<BKT>::TM, TN = WTile<BKT>::TN, FM = WTile<BKT>::FM, FN = WTile<BKT>::FN;
     __shared__ uint4 As[2][TR_BK * TR_ROW];
     __shared__ uint4 Bs[2][TR_BK * TR_ROW];
-    __shared__ int list_s[LIST_CAP];   // compacted: the split's live pixels
+    __shared__ int list_s[kCompactListCap];   // compacted: the split's live pixels
 
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;

@@ -33,6 +33,8 @@ constexpr int kDataMaxClasses = 16;
 // Chunks per split from which the bf16 weight gradient may compact dY's live
 // pixels, and the blocks per split it has to save.
 constexpr int kCompactMinChunks = 16, kCompactMinSaved = 4;
+// Pixels per compacted block, and the live pixels a workgroup can list.
+constexpr int kCompactPixels = 64, kCompactListCap = 7168;
 // Compaction groups (channel tiles) the gather mode handles; wider layers
 // run the masked data gradient without compaction (footprint select only).
 constexpr int kGatherMaxGroups = 16;
@@ -77,4 +79,26 @@ constexpr int data_rows_pick(const int* tiles, int bn, int slots, int cap = 0x7f
         }
     }
     return best;
+}
+
+// The compacted weight gradient's blocks of split z: `total` live pixels of a
+// k tile make blocks of kCompactPixels ranks, every split but the last ones
+// takes the same number of them in order, and a split past the last block
+// none.  [begin, end) blocks holding the ranks [first, last); the block past
+// the last rank is filled up, (end - begin) * kCompactPixels list entries in
+// all.
+struct CompactShare {
+    int blocks, share;         // of the tile, and of every split at most
+    int begin, end, first, last;
+};
+constexpr CompactShare compact_share(int total, int nsplit, int z)
+{
+    CompactShare s{};
+    s.blocks = (total + kCompactPixels - 1) / kCompactPixels;
+    s.share = (s.blocks + nsplit - 1) / nsplit;
+    s.begin = z * s.share < s.blocks ? z * s.share : s.blocks;
+    s.end = s.begin + s.share < s.blocks ? s.begin + s.share : s.blocks;
+    s.first = s.begin * kCompactPixels < total ? s.begin * kCompactPixels : total;
+    s.last = s.end * kCompactPixels < total ? s.end * kCompactPixels : total;
+    return s;
 }
