@@ -122,6 +122,7 @@ void data_gemm_params(const cbw_conv_desc* desc, const DataPlan& plan, const voi
         p.lists = at<int32_t>(ws, plan.lists);
         p.counts = at<int32_t>(ws, plan.counts);
         p.dead_flags = cp.dead_flags;
+        p.all_rows = at<int>(ws, plan.header) + kAllRowsWord;
     }
     *out = p;
     *cpo = cp;
@@ -911,11 +912,13 @@ int cbw_read_stats(const cbw_conv_desc* desc, int op, const void* workspace, siz
         DataPlan plan;
         if ((st = plan_data(desc, op == CBW_OP_BWD_DATA_MASKED, &plan)) != CBW_OK) return st;
         if (workspace_bytes < plan.total) return CBW_ERR_WORKSPACE;
-        int header = 0;
-        hipError_t e = hipMemcpyAsync(&header, at<void>(const_cast<void*>(workspace), plan.header), sizeof(int),
+        int hdr[2] = {0, 0};
+        hipError_t e = hipMemcpyAsync(hdr, at<void>(const_cast<void*>(workspace), plan.header), sizeof(hdr),
                                       hipMemcpyDeviceToHost, s);
         if (e == hipSuccess) e = hipStreamSynchronize(s);
         if (e != hipSuccess) return hip_status(e);
+        const int header = hdr[0];
+        const bool all_rows = hdr[kAllRowsWord] != 0;   // pixel classes: the lists hold fewer rows than were run
         r.rows_total = (int64_t)plan.groups * plan.npix;
         r.rows_live = r.rows_total;
         if (plan.rows && header == MODE_ROWS) {
@@ -944,7 +947,7 @@ int cbw_read_stats(const cbw_conv_desc* desc, int op, const void* workspace, siz
                 for (int i = 0; i < n; ++i) live += buf[i];
             }
             r.rows_live = live * plan.groups;
-        } else if (op == CBW_OP_BWD_DATA_MASKED && header == MODE_GATHER) {
+        } else if (op == CBW_OP_BWD_DATA_MASKED && header == MODE_GATHER && !all_rows) {
             int32_t counts[64];
             int64_t live = 0;
             for (int g0 = 0; g0 < plan.groups; g0 += 64) {

@@ -703,6 +703,7 @@ __global__ __launch_bounds__(Tile<TI>::NT) void bwd_data_kernel(ParamsFor<UNIT> 
             for (int g = 0; g < p.ctiles; ++g) tiles += (gtot_s[g] + BN - 1) / BN;
             relist = !all && classes_win(p, tiles, nsteps);
             all |= relist;
+            if (relist && blockIdx.x == 0 && tid == 0) *p.all_rows = 1;
         }
         map_item(__builtin_amdgcn_readfirstlane((int)all) != 0);
         if (active) start_item();
@@ -974,7 +975,10 @@ __global__ __launch_bounds__(256) void data_prep_kernel(const T* __restrict__ w,
                                                         CompactParams cp, int ncb, OccParams op)
 {
     if ((int)blockIdx.x < ntb) {
-        if (blockIdx.x == 0 && threadIdx.x == 0) header[0] = mode;
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            header[0] = mode;
+            header[kAllRowsWord] = 0;
+        }
         transform_filters<T>(w, wt, K, C, RS, krsc, (int64_t)blockIdx.x * 256 + threadIdx.x);
         return;
     }

@@ -38,6 +38,23 @@ def _gpu():
     cb.lib()
 
 
+def _rows(desc, st, pd, dt, live):
+    """GEMM rows of the skipping call with `live` pixels per channel group: all
+    of them where the class tiling's steps (eight more a tile) are fewer than
+    the live lists', which walk every tap."""
+    N, C, H, W, K, R, S = desc.N, desc.C, desc.H, desc.W, desc.K, desc.R, desc.S
+    bm, bn, _ = cb.cbw_data_tiling(desc)
+    kc, groups, npix = -(-K // (64 if dt == "bf16" else 32)), -(-C // bm), N * H * W
+    cost = 0
+    for a in range(st[0]):
+        for b in range(st[1]):
+            pix = N * sum((h + pd[0]) % st[0] == a for h in range(H)) * sum((w + pd[1]) % st[1] == b for w in range(W))
+            cost += -(-pix // bn) * groups * (len(range(a, R, st[0])) * len(range(b, S, st[1])) * kc + 8)
+    listed = sum(-(-n // bn) for n in live)
+    classes = st[0] * st[1] <= 16 and listed * (R * S * kc + 8) > cost
+    return groups * npix if classes or min(live) == npix else sum(live)
+
+
 @pytest.mark.parametrize("dead", [False, True, "few", "most"], ids=["live", "dead_pixels", "few_dead", "most_dead"])
 @pytest.mark.parametrize("case", CASES, ids=lambda c: "%s_N%dC%dK%d_%dx%d_f%dx%d_s%dx%d" % (
     c[9], c[0], c[1], c[4], c[2], c[3], c[5], c[6], *c[7]))
@@ -62,11 +79,15 @@ def test_strided_dx(case, dead):
     cb.conv_bwd_data(desc, dy.cuda(), w.cuda(), dx["dense"], ws)
     cb.conv_bwd_data_masked(desc, dy.cuda(), w.cuda(), xm, dx["select"], ws, cb.CBW_FLAG_NO_SKIP)
     cb.conv_bwd_data_masked(desc, dy.cuda(), w.cuda(), xm, dx["masked"], ws)
+    stats = cb.cbw_read_stats(desc, cb.CBW_OP_BWD_DATA_MASKED, ws)
     lists = [cb.cbw_read_live_lists(desc, ws, g) for g in range(-(-C // cb.cbw_read_live_lists(desc, ws, 0)[1]))]
     torch.cuda.synchronize()
     for g, (got, width) in enumerate(lists):
         live = (x[..., g * width:(g + 1) * width] > 0).any(dim=3).flatten().nonzero().flatten()
         assert np.array_equal(np.asarray(got), live.numpy())
+    # the rows that were computed: every pixel's where the classes ran
+    assert stats.rows_total == len(lists) * N * H * W
+    assert stats.rows_live == _rows(desc, st, pd, dt, [len(got) for got, _ in lists])
     dy64 = oracle.nhwc_to_nchw(dy.double().numpy())
     w64 = oracle.krsc_to_kcrs(w.double().numpy())
     ref, ab, nt = oracle.conv_bwd_data(dy64, w64, (H, W), st, pd, with_bound=True)
