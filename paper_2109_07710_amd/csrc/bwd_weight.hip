@@ -362,9 +362,12 @@ __global__ __launch_bounds__(F32_NW * 64, 3) void bwd_weight_f32_kernel(WeightPa
 
     // Walk over a chunk's pixels, 4 at a time, one per lane group: the lane's
     // pixel, its column q and X column w, and the byte offsets of its loads
-    // (kOOB past the tensors; the steps added to that stay out of range).
-    // Along an image row they advance by constants; a lane that leaves its
-    // row decodes its pixel anew.
+    // (y_off is kOOB past the tensor, and the steps of a chunk, 128 bytes times
+    // K, stay out of range).  Along an image row they advance by constants; a
+    // lane that leaves its row decodes its pixel anew.  A row that does not
+    // exist starts at kOOB, so that each of its columns 0 .. W - 1 lies out of
+    // range wherever in the padding the lane started (columns there can be
+    // 2^31 bytes apart).
     int pix = 0, q = 0, w = 0;
     uint32_t x_off = kOOB, y_off = kOOB;
     const uint32_t x_adv = (uint32_t)(4 * p.stride_w * p.C) * 4u, y_adv = (uint32_t)(4 * p.K) * 4u;
@@ -375,7 +378,7 @@ __global__ __launch_bounds__(F32_NW * 64, 3) void bwd_weight_f32_kernel(WeightPa
         const int h = ((int)nq - (int)n * p.P) * p.stride_h - p.pad_h + r;
         w = q * p.stride_w - p.pad_w + s;
         const bool in = pix < p.npq && c_in && (unsigned)h < (unsigned)p.H;
-        x_off = in ? (uint32_t)((((int)n * p.H + h) * p.W + w) * p.C + cc) * 4u : kOOB;
+        x_off = (uint32_t)(((in ? ((int)n * p.H + h) * p.W : 0) + w) * p.C + cc) * 4u + (in ? 0u : kOOB);
     };
     auto begin_chunk = [&](int chunk, int end) {
         if (chunk < end) {

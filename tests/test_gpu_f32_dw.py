@@ -1,8 +1,9 @@
 """GPU parity of the float32 weight gradient against the fp64 oracle: widths
 around the 64-column parts and the 256-channel tiles, images narrower than the
 four pixels of a step, chunks that cross rows and images, a ragged last chunk,
-strides and pads, several splits, and runs of dead chunks longer than one
-ballot (64 chunks per wave), skipped and not.
+strides and pads (also so wide that the columns of a row span more than 2^31
+bytes), several splits, and runs of dead chunks longer than one ballot (64
+chunks per wave), skipped and not.
 """
 import numpy as np
 import pytest
@@ -21,6 +22,7 @@ CASES = [
     (2, 68, 9, 33, 64, 3, 3, (2, 2), (1, 1), 1),
     (2, 260, 8, 10, 260, 1, 1, (1, 1), (0, 0), 0),   # two tiles of 256 along both
     (5, 128, 13, 11, 60, 2, 3, (1, 2), (0, 2), 2),
+    (1, 1 << 20, 1, 1, 4, 1, 1, (1, 32), (1, 512), 0),   # columns of the padding 2^31 bytes from the image
     (9, 32, 40, 64, 16, 3, 3, (1, 1), (1, 1), 7),    # 720 chunks, 560 of them dead in one run
 ]
 
