@@ -6,6 +6,8 @@
 // apart from the path itself.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "kernels.hpp"
 
 namespace cbw {
@@ -143,21 +145,28 @@ struct LayoutJobs {
     struct Job {
         const void* src;
         void* dst;
-        int end;                // workgroups of the jobs up to this one
+        uint32_t end;           // workgroups of the jobs up to this one
         int kind;               // 0 transpose, 1 footprint bits by ballots, 2 footprint bits, any C
         int batch, rows, cols;  // bits: N, C, H * W
         int gx, gy;             // workgroups along columns and rows
     } job[kLayoutMaxJobs];
     int n;
 };
+// Workgroups along the grid's first axis, whose threads are limited to 2^32 - 1
+// (eight million images of one pixel are as many workgroups a tensor); the
+// rest go along the second.
+constexpr uint32_t kLayoutGridX = 1u << 20;
 
 template <typename T>
 __global__ __launch_bounds__(256) void layout_kernel(LayoutJobs p)
 {
-    int j = 0, begin = 0;
-    while (j + 1 < p.n && (int)blockIdx.x >= p.job[j].end) begin = p.job[j++].end;
+    const uint32_t block = blockIdx.y * kLayoutGridX + blockIdx.x;
+    if (block >= p.job[p.n - 1].end) return;
+    int j = 0;
+    uint32_t begin = 0;
+    while (j + 1 < p.n && block >= p.job[j].end) begin = p.job[j++].end;
     const LayoutJobs::Job& q = p.job[j];
-    const int b = (int)blockIdx.x - begin;
+    const int b = (int)(block - begin);
     const int bx = b % q.gx, rest = b / q.gx;
     if (q.kind == 0) {
         transpose_block<T, 64, 64, 256>(static_cast<const T*>(q.src), static_cast<T*>(q.dst), q.rows, q.cols, bx,
@@ -203,12 +212,14 @@ hipError_t launch_layout(int dtype, const LayoutJob* jobs, int n, hipStream_t s)
             blocks += (((int64_t)in.batch * in.rows * in.cols + 31) / 32 + 255) / 256;
         }
         if (blocks > 0x7fffffff) return hipErrorInvalidValue;
-        q.end = (int)blocks;
+        q.end = (uint32_t)blocks;
         ++p.n;
     }
     if (blocks == 0) return hipSuccess;
-    if (dtype == 1) layout_kernel<uint16_t><<<(int)blocks, 256, 0, s>>>(p);
-    else layout_kernel<float><<<(int)blocks, 256, 0, s>>>(p);
+    const dim3 grid((unsigned)std::min<int64_t>(blocks, kLayoutGridX),
+                    (unsigned)((blocks + kLayoutGridX - 1) / kLayoutGridX));
+    if (dtype == 1) layout_kernel<uint16_t><<<grid, 256, 0, s>>>(p);
+    else layout_kernel<float><<<grid, 256, 0, s>>>(p);
     return hipGetLastError();
 }
 

@@ -133,3 +133,29 @@ def test_nchw_against_oracle(case):
     assert not (~mask & (bits != 0)).any(), "dead outputs must be +0.0"
     rw, aw, nw = oracle.conv_bwd_weight(x64, dy64, (spec.R, spec.S), st, pd, with_bound=True)
     check_values(dw.double().cpu().numpy(), rw, aw, nw, tol, False, "NCHW dW")
+
+
+def test_more_images_than_one_grid_axis_holds():
+    """Eight million images of one pixel, where the conversion takes a workgroup
+    per image and tensor: 2^24 and more in all, past the 2^32 - 1 threads of a
+    grid's first axis.  With one pixel both layouts are the same bytes, so
+    every result equals the NHWC call's bit for bit."""
+    N, C = (1 << 23) + 5, 8
+    print("\n[case] nchw, %d images of one pixel" % N, flush=True)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    x = torch.randn((N, C), generator=g, device="cuda").relu_().bfloat16()
+    dy = torch.randn((N, C), generator=g, device="cuda").bfloat16()
+    w = torch.randn((C, C), generator=g, device="cuda").bfloat16()
+    out = {}
+    for layout in ("nhwc", "nchw"):
+        d = cb.ConvDesc.make(N, C, 1, 1, C, 1, 1, 1, 0, act_layout=layout)
+        xm = torch.zeros(cb.cbw_mask_words(d), dtype=torch.int32, device="cuda")
+        cb.cbw_relu_mask_pack(d, x, xm)
+        dx = torch.full_like(x, float("nan"))
+        dw = torch.full((C, C), float("nan"), device="cuda")
+        cb.conv_bwd_sparse(d, x, dy, w, xm, None, dx, dw, cb.workspace(d, cb.CBW_OP_BWD_BOTH))
+        out[layout] = dx, dw
+    torch.cuda.synchronize()
+    for a, b in zip(out["nhwc"], out["nchw"]):
+        assert torch.equal(a, b)   # (no NaN left either: they would not be equal)
