@@ -122,7 +122,7 @@ void data_gemm_params(const cbw_conv_desc* desc, const DataPlan& plan, const voi
         p.lists = at<int32_t>(ws, plan.lists);
         p.counts = at<int32_t>(ws, plan.counts);
         p.dead_flags = cp.dead_flags;
-        p.all_rows = at<int>(ws, plan.header) + kAllRowsWord;
+        p.rows_run = at<int32_t>(ws, plan.header) + kRowsRunWord;
     }
     *out = p;
     *cpo = cp;
@@ -912,13 +912,11 @@ int cbw_read_stats(const cbw_conv_desc* desc, int op, const void* workspace, siz
         DataPlan plan;
         if ((st = plan_data(desc, op == CBW_OP_BWD_DATA_MASKED, &plan)) != CBW_OK) return st;
         if (workspace_bytes < plan.total) return CBW_ERR_WORKSPACE;
-        int hdr[2] = {0, 0};
-        hipError_t e = hipMemcpyAsync(hdr, at<void>(const_cast<void*>(workspace), plan.header), sizeof(hdr),
+        int header = 0;
+        hipError_t e = hipMemcpyAsync(&header, at<void>(const_cast<void*>(workspace), plan.header), sizeof(int),
                                       hipMemcpyDeviceToHost, s);
         if (e == hipSuccess) e = hipStreamSynchronize(s);
         if (e != hipSuccess) return hip_status(e);
-        const int header = hdr[0];
-        const bool all_rows = hdr[kAllRowsWord] != 0;   // pixel classes: the lists hold fewer rows than were run
         r.rows_total = (int64_t)plan.groups * plan.npix;
         r.rows_live = r.rows_total;
         if (plan.rows && header == MODE_ROWS) {
@@ -947,13 +945,15 @@ int cbw_read_stats(const cbw_conv_desc* desc, int op, const void* workspace, siz
                 for (int i = 0; i < n; ++i) live += buf[i];
             }
             r.rows_live = live * plan.groups;
-        } else if (op == CBW_OP_BWD_DATA_MASKED && header == MODE_GATHER && !all_rows) {
+        } else if (op == CBW_OP_BWD_DATA_MASKED && header == MODE_GATHER) {
+            // with pixel classes the live counts may be fewer than the rows run
+            void* wsp = const_cast<void*>(workspace);
+            const int32_t* run = plan.ncls > 0 ? at<int32_t>(wsp, plan.header) + kRowsRunWord : at<int32_t>(wsp, plan.counts);
             int32_t counts[64];
             int64_t live = 0;
             for (int g0 = 0; g0 < plan.groups; g0 += 64) {
                 const int n = plan.groups - g0 < 64 ? plan.groups - g0 : 64;
-                e = hipMemcpyAsync(counts, at<int32_t>(const_cast<void*>(workspace), plan.counts) + g0,
-                                   n * sizeof(int32_t), hipMemcpyDeviceToHost, s);
+                e = hipMemcpyAsync(counts, run + g0, n * sizeof(int32_t), hipMemcpyDeviceToHost, s);
                 if (e == hipSuccess) e = hipStreamSynchronize(s);
                 if (e != hipSuccess) return hip_status(e);
                 for (int i = 0; i < n; ++i) live += counts[i];

@@ -703,7 +703,7 @@ __global__ __launch_bounds__(Tile<TI>::NT) void bwd_data_kernel(ParamsFor<UNIT> 
             for (int g = 0; g < p.ctiles; ++g) tiles += (gtot_s[g] + BN - 1) / BN;
             relist = !all && classes_win(p, tiles, nsteps);
             all |= relist;
-            if (relist && blockIdx.x == 0 && tid == 0) *p.all_rows = 1;
+            if (blockIdx.x == 0 && tid < p.ctiles) p.rows_run[tid] = relist ? p.npix : gtot_s[tid];
         }
         map_item(__builtin_amdgcn_readfirstlane((int)all) != 0);
         if (active) start_item();
@@ -711,6 +711,7 @@ __global__ __launch_bounds__(Tile<TI>::NT) void bwd_data_kernel(ParamsFor<UNIT> 
         __syncthreads();
     } else if (MODE == MODE_GATHER && blockIdx.x == 0 && tid < p.ctiles) {
         p.counts[tid] = p.npix;   // every pixel live
+        if constexpr (!UNIT) p.rows_run[tid] = p.npix;
     }
     if (!active) return;   // uniform across the workgroup
     auto main_loop = [&](auto nb_tag) {
@@ -975,10 +976,7 @@ __global__ __launch_bounds__(256) void data_prep_kernel(const T* __restrict__ w,
                                                         CompactParams cp, int ncb, OccParams op)
 {
     if ((int)blockIdx.x < ntb) {
-        if (blockIdx.x == 0 && threadIdx.x == 0) {
-            header[0] = mode;
-            header[kAllRowsWord] = 0;
-        }
+        if (blockIdx.x == 0 && threadIdx.x == 0) header[0] = mode;
         transform_filters<T>(w, wt, K, C, RS, krsc, (int64_t)blockIdx.x * 256 + threadIdx.x);
         return;
     }
@@ -1047,15 +1045,16 @@ __device__ __forceinline__ void data_reduce_block(const ParamsFor<UNIT>& p, int 
     // the GEMM has read the dead-pixel flags: lower them for the next call
     if (MODE == MODE_GATHER && block == 0 && (int)threadIdx.x < p.ctiles) p.dead_flags[threadIdx.x] = 0;
     int ntiles, nsplit;
-    bool dense_map = MODE != MODE_GATHER;   // gather mode with every pixel live tiles like the dense mode
+    bool dense_map = MODE != MODE_GATHER;   // gather mode with every pixel run tiles like the dense mode
+    const int32_t* __restrict__ counts = p.counts;
+    if constexpr (!UNIT) counts = p.rows_run;
     if (MODE == MODE_GATHER) {
         ntiles = 0;
         bool all = true;
         for (int g = 0; g < p.ctiles; ++g) {
-            ntiles += (p.counts[g] + BN - 1) / BN;
-            all &= p.counts[g] == p.npix;
+            ntiles += (counts[g] + BN - 1) / BN;
+            all &= counts[g] == p.npix;
         }
-        if constexpr (!UNIT) all = all || classes_win(p, ntiles, nsteps);
         if (all) ntiles = p.ptiles * p.ctiles;   // the dense tiling
         nsplit = all ? p.split : data_split(ntiles, nsteps, p.nslots, p.smax);
         dense_map = all;
@@ -1068,13 +1067,18 @@ __device__ __forceinline__ void data_reduce_block(const ParamsFor<UNIT>& p, int 
     if (nsplit <= 1) return;
     const int64_t nvec = (int64_t)ntiles * BN * (BM / 4);
     T* __restrict__ dx = reinterpret_cast<T*>(p.dx);
-    for (int64_t v = (int64_t)block * 256 + threadIdx.x; v < nvec; v += (int64_t)nblocks * 256) {
+    for (int64_t v0 = (int64_t)block * 256; v0 < nvec; v0 += (int64_t)nblocks * 256) {
+        // the 256 vectors a workgroup takes at a time lie in one tile: with
+        // strides its class is found on the scalar unit (per lane, 84
+        // registers left five waves a SIMD; now 75 and six, as without classes)
+        static_assert(BN * (BM / 4) % 256 == 0, "256 vectors of one tile");
+        const int64_t v = UNIT ? v0 + threadIdx.x : v0;
         const int tile = (int)(v / (BN * (BM / 4)));
-        const int rem = (int)(v - (int64_t)tile * BN * (BM / 4));
+        const int rem = (int)(v - (int64_t)tile * BN * (BM / 4)) + (UNIT ? 0 : (int)threadIdx.x);
         const int pr = rem / (BM / 4), cl = (rem - pr * (BM / 4)) * 4;
         int ctile, ptile;
         if (!dense_map) {
-            gather_tile(p.counts, p.ctiles, BN, tile, ctile, ptile);
+            gather_tile(counts, p.ctiles, BN, tile, ctile, ptile);
         } else {
             ptile = tile / p.ctiles;
             ctile = tile - ptile * p.ctiles;
@@ -1093,7 +1097,7 @@ __device__ __forceinline__ void data_reduce_block(const ParamsFor<UNIT>& p, int 
         }
         if (UNIT || !classed) {
             const int r = ptile * BN + pr;
-            const int nrows = dense_map ? p.npix : p.counts[ctile];
+            const int nrows = dense_map ? p.npix : counts[ctile];
             if (r >= nrows || c >= p.C) continue;
             // (a fully live group's list is 0, 1, 2, ... and is not stored)
             pix = nrows < p.npix ? p.lists[(int64_t)ctile * p.npix + r] : r;

@@ -96,15 +96,16 @@ struct DataParams {
 // The same with the pixel classes, for strides above 1 (a type of its own:
 // carrying a kilobyte of classes through every launch cost the unit-stride
 // split reduction 3 us).
-constexpr int kAllRowsWord = 1;     // data workspace header word that all_rows points to
+constexpr int kRowsRunWord = 8;     // data workspace header words from here: rows_run, one per channel group
+static_assert(4 * (kRowsRunWord + kGatherMaxGroups) <= 256, "rows_run fits the header");
 constexpr int kDataTileSteps = 8;   // what starting and finishing a tile costs, in steps
 struct DataParamsStrided : DataParams {
     int ncls;                // 0: every tap of every pixel
     int64_t cls_cost;        // steps of the class tiling, every tile kDataTileSteps on top
-    // gather mode: set where the class tiling ran over dead pixels too (the
-    // preparation launch clears it), so that the statistics tell its rows
-    // from the live lists'
-    int* all_rows;
+    // gather mode: the rows run per channel group, for the reduction and the
+    // statistics: every pixel where the class tiling ran over dead ones too,
+    // else the live counts (which stay in counts for the list readers)
+    int32_t* rows_run;
     DataClass cls[kDataMaxClasses];   // most taps first
 };
 
@@ -235,7 +236,6 @@ int compact_block_pixels();
 // Filter transform (and, when cp is given, the compaction counts and the
 // dead-row zero fill; when op is given, the weight gradient's dY block
 // occupancy) in one launch.
-// header[0] = mode, header[kAllRowsWord] = 0.
 hipError_t launch_data_prep(int dtype, const void* w, void* wt, int K, int C, int RS, int krsc, int* header,
                             int mode, const CompactParams* cp, hipStream_t stream, const OccParams* op = nullptr);
 // The data-gradient GEMM and, when its reduction may be split, the launch
