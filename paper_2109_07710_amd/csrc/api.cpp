@@ -97,6 +97,7 @@ void data_gemm_params(const cbw_conv_desc* desc, const DataPlan& plan, const voi
     p.smax = no_split ? 1 : kDataMaxSplit;
     p.split = plan.split;   // gather mode: the split of its dense tiles, which it checks on the device
     p.ncls = plan.ncls;
+    p.ptaps = plan.ptaps;
     for (int c = 0; c < plan.ncls; ++c) {
         const DataPlan::Class& k = plan.cls[c];
         p.cls[c] = DataClass{k.tile0, (int)k.npix, k.nh, k.nw, k.i0, k.j0, k.a, k.b, k.nr, k.ns,

@@ -235,7 +235,8 @@ __device__ void gather_list(const DataParams& p, int G, int g, int row0, int row
 // (walking all R * S taps of every pixel runs stride_h * stride_w times the
 // products that land).  3x3 stride 2, N = 32, masked: 128 -> 256 channels at
 // 56x56 62 -> 35 us, 256 -> 512 168 -> 71 us, 64 -> 128 at 112x112 125 -> 56 us; 1x1
-// stride 2, where three classes of four have no tap, 24.3 -> 23 us.
+// stride 2, where three classes of four have no tap, 24.3 -> 23 us with their
+// tiles split like the others, which they no longer are.
 
 // The class a pixel tile of the dense tiling belongs to.
 __device__ __forceinline__ int tile_class(const DataParamsStrided& p, int ptile)
@@ -383,15 +384,30 @@ __global__ __launch_bounds__(Tile<TI>::NT) void bwd_data_kernel(ParamsFor<UNIT> 
         // for the most tiles any row choice gives); the surplus has no item,
         // and the XCD remap runs over the items alone so that every XCD gets
         // its share.
-        const int nitems = ntiles * nsplit;
+        int nitems = ntiles * nsplit;
+        // (tiles that no tap reaches, the last ones, are not split)
+        int nsplit_items = nitems;
+        if constexpr (!UNIT) {
+            if (dense_rule) {
+                nsplit_items = data_split_tiles(p) * nsplit;
+                nitems = nsplit_items + ntiles - data_split_tiles(p);
+            }
+        }
         active = (int)blockIdx.x < nitems;   // uniform across the workgroup
         if (!active) return;
         // classes differ in steps and come longest first: taken in dispatch
         // order, so that every XCD gets its share of each
         if constexpr (!UNIT) classed = dense_rule && p.ncls > 0;
         item = classed ? (int)blockIdx.x : xcd_remap(blockIdx.x, nitems);
-        const int tile = item / nsplit;
-        z = item - tile * nsplit;
+        int tile;
+        if (UNIT || item < nsplit_items) {
+            tile = item / nsplit;
+            z = item - tile * nsplit;
+        } else {
+            tile = ntiles - (nitems - item);
+            z = 0;
+            nsplit = 1;
+        }
         if (dense_rule) {
             ptile = tile / p.ctiles;
             ctile = tile - ptile * p.ctiles;
@@ -1055,11 +1071,11 @@ __device__ __forceinline__ void data_reduce_block(const ParamsFor<UNIT>& p, int 
             ntiles += (counts[g] + BN - 1) / BN;
             all &= counts[g] == p.npix;
         }
-        if (all) ntiles = p.ptiles * p.ctiles;   // the dense tiling
+        if (all) ntiles = data_split_tiles(p);   // the dense tiling
         nsplit = all ? p.split : data_split(ntiles, nsteps, p.nslots, p.smax);
         dense_map = all;
     } else {
-        ntiles = p.ptiles * p.ctiles;
+        ntiles = data_split_tiles(p);
         nsplit = p.split;
     }
     // A split reduction only happens with full BN-row tiles (data_rows_pick
@@ -1169,13 +1185,14 @@ __global__ __launch_bounds__(256) void splitk_data_reduce_kernel(ParamsFor<UNIT>
 // (decided on the device, over at most half that many tiles) with a few
 // vectors per thread.  Each vector's loads are one chain of latency, so the
 // grid follows the work rather than a fixed size.
-int data_reduce_blocks(const DataParams& p)
+template <typename P>
+int data_reduce_blocks(const P& p)
 {
     int64_t nvec = 0;
     if (p.split > 1) {
         const int bm = p.tile == 0 ? Tile<0>::BM : p.tile == 1 ? Tile<1>::BM : Tile<2>::BM;
         const int bn = p.tile == 0 ? Tile<0>::BN : p.tile == 1 ? Tile<1>::BN : Tile<2>::BN;
-        nvec = (int64_t)p.ptiles * p.ctiles * bn * (bm / 4);
+        nvec = (int64_t)data_split_tiles(p) * bn * (bm / 4);
     }
     return (int)std::max<int64_t>(p.nslots, (nvec + 255) / 256);
 }
@@ -1285,7 +1302,8 @@ hipError_t launch_type(int mode, const DataParamsStrided& p, int nb, hipStream_t
 hipError_t launch_bwd_data(int dtype, int mode, const DataParamsStrided& p, hipStream_t stream, const ProfEvents& ev)
 {
     // enough workgroups for every tile of the dense tiling unsplit, or for
-    // nslots split items.  Gather mode fits too: with at most as many live
+    // nslots split items (the tiles that no tap reaches among them, see the
+    // planner's split).  Gather mode fits too: with at most as many live
     // pixels per group its tiles at the dense row count are no more, its row
     // choice is capped at the dense tile count, and a split tiling has at
     // most nslots items.

@@ -101,6 +101,7 @@ static_assert(4 * (kRowsRunWord + kGatherMaxGroups) <= 256, "rows_run fits the h
 constexpr int kDataTileSteps = 8;   // what starting and finishing a tile costs, in steps
 struct DataParamsStrided : DataParams {
     int ncls;                // 0: every tap of every pixel
+    int ptaps;               // pixel tiles that a tap reaches, the first of ptiles; the others are not split
     int64_t cls_cost;        // steps of the class tiling, every tile kDataTileSteps on top
     // gather mode: the rows run per channel group, for the reduction and the
     // statistics: every pixel where the class tiling ran over dead ones too,
@@ -108,6 +109,9 @@ struct DataParamsStrided : DataParams {
     int32_t* rows_run;
     DataClass cls[kDataMaxClasses];   // most taps first
 };
+// Tiles of the dense tiling whose reduction is split (when it is).
+__host__ __device__ inline int data_split_tiles(const DataParams& p) { return p.ptiles * p.ctiles; }
+__host__ __device__ inline int data_split_tiles(const DataParamsStrided& p) { return p.ptaps * p.ctiles; }
 
 // Row-window data gradient (3 x 3, stride 1, C = K = 64, bf16, NHWC): a
 // workgroup per (column segment, strip of rows_per_strip output rows).

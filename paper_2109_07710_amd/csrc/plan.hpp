@@ -33,6 +33,7 @@ struct DataPlan {
     int64_t npix = 0;
     int groups = 0, nblk = 0;
     int ptiles = 0, nsteps = 0;
+    int ptaps = 0;          // pixel tiles that a tap reaches, the first of ptiles (all, without classes)
     int brows = 0;          // dense / select: pixel rows per tile (data_rows_pick)
     int split = 1;          // dense / select: host-chosen reduction split
     // stride > 1: pixel classes (see DataClass), most taps first; 0 when the
@@ -71,11 +72,12 @@ bool data_rows_eligible(const cbw_conv_desc* d);
 bool data_pw_eligible(const cbw_conv_desc* d);
 constexpr int kDataMaxSplit = 16;
 
-// Same rule as the kernels' data_split (see common.hpp).
-inline int host_data_split(int T, int nsteps)
+// Same rule as the kernels' data_split (see common.hpp), for T tiles beside
+// `unsplit` that stay whole.
+inline int host_data_split(int T, int nsteps, int unsplit = 0)
 {
-    if (T <= 0 || 2 * T > kDataSlots) return 1;
-    int sp = kDataSlots / T;
+    if (T <= 0 || 2 * (T + unsplit) > kDataSlots) return 1;
+    int sp = (kDataSlots - unsplit) / T;
     if (sp > kDataMaxSplit) sp = kDataMaxSplit;
     if (sp > nsteps) sp = nsteps;
     return sp < 1 ? 1 : sp;

@@ -13,4 +13,14 @@ void probe_compact_share(int total, int nsplit, int z, int32_t* out)
     out[0] = s.blocks; out[1] = s.share; out[2] = s.begin; out[3] = s.end; out[4] = s.first; out[5] = s.last;
 }
 
+// tile channels, tile rows, groups, ptiles, ptaps, split, then the partial region's bytes
+int probe_data_plan(const cbw_conv_desc* d, int masked, int64_t* out)
+{
+    cbw::DataPlan p;
+    const int st = cbw::plan_data(d, masked != 0, &p);
+    const int64_t v[] = {p.bm, p.brows, p.groups, p.ptiles, p.ptaps, p.split, (int64_t)p.partial.bytes};
+    for (int i = 0; i < 7; ++i) out[i] = v[i];
+    return st;
+}
+
 }  // extern "C"

@@ -19,6 +19,9 @@ CASES = [
     # N, C, H, W, K, R, S, stride, pad, dtype
     (2, 64, 13, 11, 40, 3, 3, (2, 2), (1, 1), "bf16"),      # few tiles: split reduction
     (3, 72, 9, 10, 136, 1, 1, (2, 2), (0, 0), "bf16"),      # three classes of four have no tap
+    (3, 256, 27, 27, 256, 1, 1, (2, 2), (0, 0), "bf16"),    # their tiles whole beside split ones
+    (1, 64, 1, 40, 128, 1, 1, (2, 2), (1, 0), "bf16"),      # no pixel has a tap
+    (3, 72, 23, 20, 100, 1, 1, (2, 2), (0, 0), "f32"),
     (1, 128, 1, 37, 64, 1, 3, (2, 3), (0, 1), "bf16"),      # one row: classes without a pixel
     (2, 256, 12, 15, 64, 5, 4, (3, 1), (4, 0), "bf16"),     # nine taps at most, stride 1 along one axis
     (2, 32, 17, 9, 32, 2, 2, (4, 4), (1, 3), "bf16"),       # filter smaller than the stride, pad past the filter

@@ -7,6 +7,8 @@ import subprocess
 
 import pytest
 
+import paper_2109_07710_amd as cb
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
@@ -41,3 +43,34 @@ def test_compacted_list_indices(P, nsplit):
             ranks += last - first
             blocks += end - begin
         assert ranks == total and blocks == nblk
+
+
+@pytest.mark.parametrize("layer", [
+    # N, C, H, W, K, R, S, strides, pads
+    (3, 256, 27, 27, 256, 1, 1, (2, 2), (0, 0)),
+    (26, 256, 32, 36, 512, 1, 1, (2, 2), (0, 0)),
+    (4, 64, 112, 112, 512, 1, 1, (2, 2), (0, 0)),
+    (2, 128, 30, 21, 264, 1, 3, (2, 2), (0, 1)),
+    (2, 64, 20, 20, 128, 3, 3, (4, 4), (1, 1)),
+    (8, 128, 28, 28, 256, 3, 3, (2, 2), (1, 1)),      # every class has a tap
+    (1, 64, 1, 40, 128, 1, 1, (2, 2), (1, 0)),        # no pixel has one
+], ids=lambda v: "N%d_%dx%d_C%d_K%d_f%dx%d" % (v[0], v[2], v[3], v[1], v[4], v[5], v[6]))
+def test_tap_free_tiles_are_not_split(P, layer):
+    """Strided data gradient: tiles of pixels that no filter tap reaches have no
+    partials and take no part in the choice of the split; with them the items
+    of a split tiling are at most one a CU."""
+    N, C, H, W, K, R, S, st, pd = layer
+    d = cb.ConvDesc.make(N, C, H, W, K, R, S, st, pd)
+    out = (ctypes.c_int64 * 7)()
+    assert P.probe_data_plan(ctypes.byref(d), 0, out) == cb.CBW_OK
+    bm, rows, groups, ptiles, ptaps, split, partial = out
+    pixels = lambda size, s, pad, a: sum((h + pad) % s == a for h in range(size))  # noqa: E731
+    tiles = [(-(-N * pixels(H, st[0], pd[0], a) * pixels(W, st[1], pd[1], b) // rows), a < R and b < S)
+             for a in range(st[0]) for b in range(st[1])]
+    taps, free = (groups * sum(t for t, has in tiles if has == h) for h in (True, False))
+    assert (ptaps * groups, ptiles * groups) == (taps, taps + free)
+    assert partial == (taps * split * rows * bm * 4 if split > 1 else 0)
+    assert split == 1 or (taps and taps * split + free <= 256)
+    if 0 < taps and 2 * (taps + free) <= 256:
+        steps = -(-R // st[0]) * -(-S // st[1]) * -(-K // 64)
+        assert split == min(16, steps, (256 - free) // taps)
