@@ -5,7 +5,9 @@
 #include <algorithm>
 #include <atomic>
 #include <cstring>
+#include <memory>
 #include <mutex>
+#include <new>
 
 #include "../../include/convbwd.h"
 #include "kernels.hpp"
@@ -111,6 +113,7 @@ void data_gemm_params(const cbw_conv_desc* desc, const DataPlan& plan, const voi
         cp.mask = x_mask;
         cp.blk_counts = at<int32_t>(ws, plan.blk_counts);
         cp.dead_flags = at<int32_t>(ws, plan.dead_flags);
+        cp.live_bits = plan.live_bits.bytes ? at<uint64_t>(ws, plan.live_bits) : nullptr;
         cp.dx = dX;
         cp.npix = (int)plan.npix;
         cp.C = desc->C;
@@ -1018,6 +1021,19 @@ int cbw_read_live_lists(const cbw_conv_desc* desc, const void* workspace, size_t
     if (pixels && n == plan.npix) {
         // a fully live group's list (0, 1, 2, ...) is never stored
         for (int32_t i = 0; i < n; ++i) pixels[i] = i;
+    } else if (pixels && n > 0 && plan.live_bits.bytes) {
+        // (a GEMM over the pixel classes stores no list)
+        const size_t words = (size_t)plan.nblk * (kCompactBlock / 64);
+        const std::unique_ptr<uint64_t[]> bits(new (std::nothrow) uint64_t[words]);
+        if (!bits) return hip_status(hipErrorOutOfMemory);
+        e = hipMemcpyAsync(bits.get(), at<uint64_t>(ws, plan.live_bits) + group * words, words * 8,
+                           hipMemcpyDeviceToHost, s);
+        if (e == hipSuccess) e = hipStreamSynchronize(s);
+        if (e != hipSuccess) return hip_status(e);
+        int32_t i = 0;
+        for (size_t w = 0; w < words; ++w)
+            for (uint64_t v = bits[w]; v != 0 && i < n; v &= v - 1) pixels[i++] = (int32_t)(64 * w) + __builtin_ctzll(v);
+        if (i != n) return CBW_ERR_INVALID_ARG;   // workspace not written by a gather call
     } else if (pixels && n > 0) {
         e = hipMemcpyAsync(pixels, at<int32_t>(ws, plan.lists) + (int64_t)group * plan.npix,
                            (size_t)n * sizeof(int32_t), hipMemcpyDeviceToHost, s);

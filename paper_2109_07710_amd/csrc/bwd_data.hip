@@ -266,7 +266,10 @@ __device__ __forceinline__ int class_pixel(const DataParamsStrided& p, const Dat
 // by the steps of both (`listed` tiles of the lists).  Element-wise
 // footprints of narrow layers have a few dead pixels: 8 -> 280 channels,
 // 3x3 stride 2, 199x199, N = 3, 64% of the elements live: both gradients
-// 94.6 us over the lists, 74.8 over the classes.
+// 94.6 us over the lists, 74.8 over the classes.  The tiles of the classes are
+// those the speculation started; no list is built (building them for the
+// readers, who take the preparation launch's bits, and starting again took
+// 5 to 7 us: 128 -> 256, 125x125, N = 4, 65% of the pixels live: 88.7 -> 82.3).
 __device__ __forceinline__ bool classes_win(const DataParamsStrided& p, int listed, int nsteps)
 {
     return p.ncls > 0 && (int64_t)listed * (nsteps + kDataTileSteps) > p.cls_cost;
@@ -357,7 +360,7 @@ __global__ __launch_bounds__(Tile<TI>::NT) void bwd_data_kernel(ParamsFor<UNIT> 
     int fnw = 0, wrow0 = 0, nrows = 0, st_begin = 0, nloc = 0;
     bool active = false, listed = false;
     // the class of the item's pixels (stride > 1, not listed) and its taps
-    bool classed = false, relist = false;   // relist: classes although pixels are dead
+    bool classed = false;
     int cls = 0, taps_r = p.R, taps_s = p.S;
     uint32_t a_off[IA];   // A: byte offset without the step part, kOOB when no such channel
     // logical chunk of the lane in every row group it copies: swz8 of row
@@ -610,18 +613,6 @@ __global__ __launch_bounds__(Tile<TI>::NT) void bwd_data_kernel(ParamsFor<UNIT> 
     // (consecutive pixels, or in gather mode the group's live pixels of ranks
     // row0 .. row0 + brows - 1), the dY copies and the footprint words.
     auto start_item = [&]() {
-        if constexpr (MODE == MODE_GATHER && !UNIT) {
-            // the live lists, which no tile of the classes needs, for their readers
-            const int g = ctile, lo = ptile * BN;
-            const int live = relist && active ? __builtin_amdgcn_readfirstlane(gtot_s[g]) : p.npix;
-            const int hi = min(lo + BN, live);
-            if (z == 0 && lo < hi && live < p.npix) {
-                gather_list<NT>(p, BM, g, lo, hi, pix_s, gscr_s);
-                __syncthreads();
-                for (int i = tid; i < hi - lo; i += NT) p.lists[(int64_t)g * p.npix + lo + i] = pix_s[i];
-                __syncthreads();
-            }
-        }
         ld_tap = st_begin / kchunks;
         ld_kc = st_begin % kchunks;
         if (UNIT || nloc > 0) load_a(0, ld_tap, ld_kc * BK);
@@ -711,20 +702,22 @@ __global__ __launch_bounds__(Tile<TI>::NT) void bwd_data_kernel(ParamsFor<UNIT> 
         }
         __syncthreads();
         // (a stale flag with every pixel live keeps the dense tiling, which the
-        // split reduction takes for it)
+        // split reduction takes for it, and so do pixel classes that are cheaper
+        // than the lists: their copies are the speculative ones)
         bool all = true;
         for (int g = 0; g < p.ctiles; ++g) all &= gtot_s[g] == p.npix;
         if constexpr (MODE == MODE_GATHER && !UNIT) {
             int tiles = 0;
             for (int g = 0; g < p.ctiles; ++g) tiles += (gtot_s[g] + BN - 1) / BN;
-            relist = !all && classes_win(p, tiles, nsteps);
-            all |= relist;
-            if (blockIdx.x == 0 && tid < p.ctiles) p.rows_run[tid] = relist ? p.npix : gtot_s[tid];
+            all = all || classes_win(p, tiles, nsteps);
+            if (blockIdx.x == 0 && tid < p.ctiles) p.rows_run[tid] = all ? p.npix : gtot_s[tid];
         }
-        map_item(__builtin_amdgcn_readfirstlane((int)all) != 0);
-        if (active) start_item();
-        wait_vmem();
-        __syncthreads();
+        if (!__builtin_amdgcn_readfirstlane((int)all)) {
+            map_item(false);
+            if (active) start_item();
+            wait_vmem();
+            __syncthreads();
+        }
     } else if (MODE == MODE_GATHER && blockIdx.x == 0 && tid < p.ctiles) {
         p.counts[tid] = p.npix;   // every pixel live
         if constexpr (!UNIT) p.rows_run[tid] = p.npix;

@@ -60,7 +60,7 @@ __device__ __forceinline__ bool pixel_live(const CompactParams& p, int px, int g
 }
 
 // Counts the live pixels of compaction block `blk` of group `g` into
-// blk_counts[g][blk] and clears the dX rows of the group's dead pixels in
+// blk_counts[g][blk], records them in live_bits where given and clears the dX rows of the group's dead pixels in
 // the block (the data-gradient GEMM never visits them).  Called by a whole
 // kCompactThreads-thread block.
 __device__ __forceinline__ void compact_count_block(const CompactParams& p, int blk, int g)
@@ -76,6 +76,7 @@ __device__ __forceinline__ void compact_count_block(const CompactParams& p, int 
     if (lane == 0) {
         wc[wave] = __popcll(lb);
         wd[wave] = __popcll(db);
+        if (p.live_bits) p.live_bits[((int64_t)g * p.nblk + blk) * NWV + wave] = lb;
     }
     __syncthreads();
     int wb = 0, ndead = 0, nlive = 0;

@@ -66,6 +66,7 @@ struct DataParams {
     const uint32_t* mask;    // packed footprint of X (select / gather)
     // gather mode: the compaction counts written by the preparation launch,
     // and the outputs the GEMM writes for the reduction kernel and readers
+    // (the lists only where its tiles run over them)
     const int32_t* blk_counts;   // [groups][nblk] live pixels per 256-pixel block
     int nblk;
     int32_t* lists;          // [groups][npix] live pixels, ascending (written by the tiles of
@@ -154,6 +155,8 @@ struct CompactParams {
     const uint32_t* mask;    // packed footprint, NHWC bit order
     int32_t* blk_counts;     // [groups][nblk] live pixels per 256-pixel block
     int32_t* dead_flags;     // [groups] set to 1 by a block with a dead pixel
+    uint64_t* live_bits;     // [groups][nblk][4] live pixels, a bit each, or null: for the list
+                             // readers where the GEMM may run every pixel and store no list
     void* dx;                // zero-filled at (pixel, group) rows dead for the whole group
     int npix, C, G, groups, nblk, elem_bytes;
 };

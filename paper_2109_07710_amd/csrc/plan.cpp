@@ -229,6 +229,7 @@ int plan_data(const cbw_conv_desc* d, bool masked, DataPlan* out, bool no_split,
         p.counts = take(&cur, (size_t)p.groups * 4);
         p.dead_flags = take(&cur, (size_t)p.groups * 4);
         p.lists = take(&cur, (size_t)p.groups * p.npix * 4);
+        if (p.ncls > 0) p.live_bits = take(&cur, (size_t)p.groups * p.nblk * (kCompactBlock / 8));
     }
     // Split partial tiles.  Without skipping the host knows the split; with
     // compaction it is decided on the device, bounded by one partial tile

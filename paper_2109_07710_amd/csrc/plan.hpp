@@ -54,7 +54,7 @@ struct DataPlan {
     // the tiled GEMM and its compaction (per-workgroup counts in row_counts).
     bool pw = false;
     int pw_grid = 0, pw_bpw = 0;
-    Region header, wt, blk_counts, counts, dead_flags, lists, partial, row_counts;
+    Region header, wt, blk_counts, counts, dead_flags, lists, live_bits, partial, row_counts;
     // NCHW callers: NHWC copies of dY and dX and the NHWC-order footprint,
     // after every other region (the other offsets do not depend on layout)
     Region t_dy, t_dx, t_mask;
