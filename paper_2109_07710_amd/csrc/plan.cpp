@@ -85,6 +85,30 @@ static int data_classes(const cbw_conv_desc* d, DataPlan::Class* out)
     return n;
 }
 
+// Split of the bf16 class tiling, `most` ways at most: `tiles` tiles, `steps`
+// steps in the longest one.  The classes have few steps and, a tile row of
+// theirs being a part of an image's, many tiles, so the finest split (the rule
+// without classes) writes more partials than its shorter chains save, and
+// leaves no CU to the weight gradient's reduction in the same launch.  Fitted
+// in us: 1.1 a step, 6 for a reduction at all, the partials written and read at
+// 10 TB/s together.  Both gradients, N = 16, by the number of splits (16, 8, 4,
+// 2, 1): 512 -> 512, 3x3, 8 x 8 48.9, 48.2, 50.6, 58.0, 68.0 us; 128 -> 256,
+// 28 x 28 58.3 (9), 55.7, 52.4, 55.2, 55.2; 256 -> 512, 1x1, 28 x 28 -, 45.9,
+// 44.6, 45.0, 42.6.  fp32 steps are six times as long: as fine as it goes.
+static int class_split(int most, int tiles, int steps, double tile_mb)
+{
+    int best = 1;
+    double best_cost = 1.1 * steps;
+    for (int sp = 2; sp <= most; ++sp) {
+        const double cost = 6.0 + 1.1 * ((steps + sp - 1) / sp) + tile_mb * tiles * sp / 10.0;
+        if (cost < best_cost) {
+            best = sp;
+            best_cost = cost;
+        }
+    }
+    return best;
+}
+
 int data_tile_index(int C)
 {
     int best = 0, best_waste = -1;
@@ -222,6 +246,8 @@ int plan_data(const cbw_conv_desc* d, bool masked, DataPlan* out, bool no_split,
     // 2, 27 x 27, N = 3 (both gradients 42.3 -> 39.8 us, 41.9 without classes;
     // 69 x 72: 54.6 -> 47.3, 53.4).
     p.split = no_split ? 1 : host_data_split(p.ptaps * p.groups, split_steps, (p.ptiles - p.ptaps) * p.groups);
+    if (p.ncls > 0 && d->dtype == CBW_BF16)
+        p.split = class_split(p.split, p.ptaps * p.groups, split_steps, p.bn * p.bm * 4e-6);
     p.header = take(&cur, 256);
     p.wt = take(&cur, (size_t)d->K * d->C * d->R * d->S * elem_bytes(d->dtype));
     if (masked) {

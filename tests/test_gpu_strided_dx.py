@@ -17,9 +17,10 @@ pytestmark = pytest.mark.gpu
 
 CASES = [
     # N, C, H, W, K, R, S, stride, pad, dtype
-    (2, 64, 13, 11, 40, 3, 3, (2, 2), (1, 1), "bf16"),      # few tiles: split reduction
+    (2, 64, 13, 11, 40, 3, 3, (2, 2), (1, 1), "bf16"),      # few tiles of few steps
+    (2, 64, 13, 11, 520, 3, 3, (2, 2), (1, 1), "bf16"),     # few tiles of many: split reduction
     (3, 72, 9, 10, 136, 1, 1, (2, 2), (0, 0), "bf16"),      # three classes of four have no tap
-    (3, 256, 27, 27, 256, 1, 1, (2, 2), (0, 0), "bf16"),    # their tiles whole beside split ones
+    (3, 256, 27, 27, 1024, 1, 1, (2, 2), (0, 0), "bf16"),   # their tiles whole beside split ones
     (1, 64, 1, 40, 128, 1, 1, (2, 2), (1, 0), "bf16"),      # no pixel has a tap
     (3, 72, 23, 20, 100, 1, 1, (2, 2), (0, 0), "f32"),
     (1, 128, 1, 37, 64, 1, 3, (2, 3), (0, 1), "bf16"),      # one row: classes without a pixel

@@ -45,9 +45,11 @@ def test_compacted_list_indices(P, nsplit):
         assert ranks == total and blocks == nblk
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("layer", [
     # N, C, H, W, K, R, S, strides, pads
     (3, 256, 27, 27, 256, 1, 1, (2, 2), (0, 0)),
+    (3, 256, 27, 27, 1024, 1, 1, (2, 2), (0, 0)),
     (26, 256, 32, 36, 512, 1, 1, (2, 2), (0, 0)),
     (4, 64, 112, 112, 512, 1, 1, (2, 2), (0, 0)),
     (2, 128, 30, 21, 264, 1, 3, (2, 2), (0, 1)),
@@ -55,12 +57,13 @@ def test_compacted_list_indices(P, nsplit):
     (8, 128, 28, 28, 256, 3, 3, (2, 2), (1, 1)),      # every class has a tap
     (1, 64, 1, 40, 128, 1, 1, (2, 2), (1, 0)),        # no pixel has one
 ], ids=lambda v: "N%d_%dx%d_C%d_K%d_f%dx%d" % (v[0], v[2], v[3], v[1], v[4], v[5], v[6]))
-def test_tap_free_tiles_are_not_split(P, layer):
+def test_tap_free_tiles_are_not_split(P, layer, dtype):
     """Strided data gradient: tiles of pixels that no filter tap reaches have no
     partials and take no part in the choice of the split; with them the items
-    of a split tiling are at most one a CU."""
+    of a split tiling are at most one a CU.  bf16 splits only where the steps
+    saved outweigh the partials: fewer ways, by the cost the planner states."""
     N, C, H, W, K, R, S, st, pd = layer
-    d = cb.ConvDesc.make(N, C, H, W, K, R, S, st, pd)
+    d = cb.ConvDesc.make(N, C, H, W, K, R, S, st, pd, dtype=dtype)
     out = (ctypes.c_int64 * 7)()
     assert P.probe_data_plan(ctypes.byref(d), 0, out) == cb.CBW_OK
     bm, rows, groups, ptiles, ptaps, split, partial = out
@@ -72,5 +75,7 @@ def test_tap_free_tiles_are_not_split(P, layer):
     assert partial == (taps * split * rows * bm * 4 if split > 1 else 0)
     assert split == 1 or (taps and taps * split + free <= 256)
     if 0 < taps and 2 * (taps + free) <= 256:
-        steps = -(-R // st[0]) * -(-S // st[1]) * -(-K // 64)
-        assert split == min(16, steps, (256 - free) // taps)
+        steps = -(-R // st[0]) * -(-S // st[1]) * -(-K // (64 if dtype == "bf16" else 32))
+        most = min(16, steps, (256 - free) // taps)
+        cost = lambda n: 1.1 * -(-steps // n) + (6.0 + rows * bm * 4e-6 * taps * n / 10.0 if n > 1 else 0.0)  # noqa: E731
+        assert split == (most if dtype == "f32" else min(range(1, most + 1), key=cost))
