@@ -221,7 +221,16 @@ int plan_data(const cbw_conv_desc* d, bool masked, DataPlan* out, bool no_split,
     }
     p.brows = data_rows_pick(cand, p.bn, kDataSlots);
     p.ptiles = p.ptaps = (int)((p.npix + p.brows - 1) / p.brows);
+    const int bk = 8 * (d->dtype == CBW_BF16 ? 8 : 4);
+    p.nsteps = d->R * d->S * ((d->K + bk - 1) / bk);
     p.ncls = data_classes(d, p.cls);
+    // One step a tile in one round of tiles: the classes shorten no chain, and
+    // their tiles store every other pixel's row (both gradients of 1x1 stride 2,
+    // 53 x 53, N = 8, K = 32, C = 208, 240, 256, 328 with classes and without:
+    // 28.3, 29.0, 24.3, 31.8 and 26.3, 26.9, 24.1, 29.0 us).  Not with tiles of
+    // 64 channels, whose rows are a line or less (C = 64, 56 x 56, N = 32: 24.3
+    // and 25.1; C = 144: 28.2 and 34.7).
+    if (p.nsteps == 1 && p.bm > 64 && p.ptiles * p.groups <= kDataSlots) p.ncls = 0;
     if (p.ncls > 0) {
         // full tiles: a tile's time hardly depends on its rows, and with
         // classes of different taps rounds of tiles say little (128 -> 256
@@ -235,8 +244,6 @@ int plan_data(const cbw_conv_desc* d, bool masked, DataPlan* out, bool no_split,
             if (p.cls[c].nr * p.cls[c].ns > 0) p.ptaps = p.ptiles;
         }
     }
-    const int bk = 8 * (d->dtype == CBW_BF16 ? 8 : 4);
-    p.nsteps = d->R * d->S * ((d->K + bk - 1) / bk);
     // (classes: no finer than the longest one's steps, the rest would write
     // partials for nothing)
     const int split_steps = p.ncls > 0 ? std::max(1, p.cls[0].nr * p.cls[0].ns * (p.nsteps / (d->R * d->S))) : p.nsteps;

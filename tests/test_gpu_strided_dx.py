@@ -22,6 +22,8 @@ CASES = [
     (3, 72, 9, 10, 136, 1, 1, (2, 2), (0, 0), "bf16"),      # three classes of four have no tap
     (3, 256, 27, 27, 1024, 1, 1, (2, 2), (0, 0), "bf16"),   # their tiles whole beside split ones
     (1, 64, 1, 40, 128, 1, 1, (2, 2), (1, 0), "bf16"),      # no pixel has a tap
+    (7, 208, 41, 39, 32, 1, 1, (2, 2), (0, 0), "bf16"),     # one step a tile, one round: no classes
+    (2, 64, 21, 19, 40, 1, 1, (2, 1), (0, 0), "bf16"),      # one step, 64-channel tiles: two classes
     (3, 72, 23, 20, 100, 1, 1, (2, 2), (0, 0), "f32"),
     (1, 128, 1, 37, 64, 1, 3, (2, 3), (0, 1), "bf16"),      # one row: classes without a pixel
     (2, 256, 12, 15, 64, 5, 4, (3, 1), (4, 0), "bf16"),     # nine taps at most, stride 1 along one axis
@@ -45,9 +47,10 @@ def _gpu():
 def _rows(desc, st, pd, dt, live):
     """GEMM rows of the skipping call with `live` pixels per channel group: all
     of them where the class tiling's steps (eight more a tile) are fewer than
-    the live lists', which walk every tap."""
+    the live lists', which walk every tap.  No classes past 16 residues, and none
+    where a round of tiles of over 64 channels takes one step each."""
     N, C, H, W, K, R, S = desc.N, desc.C, desc.H, desc.W, desc.K, desc.R, desc.S
-    bm, bn, _ = cb.cbw_data_tiling(desc)
+    bm, bn, rows = cb.cbw_data_tiling(desc)
     kc, groups, npix = -(-K // (64 if dt == "bf16" else 32)), -(-C // bm), N * H * W
     cost = 0
     for a in range(st[0]):
@@ -55,7 +58,8 @@ def _rows(desc, st, pd, dt, live):
             pix = N * sum((h + pd[0]) % st[0] == a for h in range(H)) * sum((w + pd[1]) % st[1] == b for w in range(W))
             cost += -(-pix // bn) * groups * (len(range(a, R, st[0])) * len(range(b, S, st[1])) * kc + 8)
     listed = sum(-(-n // bn) for n in live)
-    classes = st[0] * st[1] <= 16 and listed * (R * S * kc + 8) > cost
+    single = R * S * kc == 1 and bm > 64 and -(-npix // rows) * groups <= 256
+    classes = st[0] * st[1] <= 16 and not single and listed * (R * S * kc + 8) > cost
     return groups * npix if classes or min(live) == npix else sum(live)
 
 
