@@ -1173,7 +1173,8 @@ __global__ __launch_bounds__(256) void splitk_data_reduce_kernel(ParamsFor<UNIT>
 }
 
 // Workgroups of the data gradient's split reduction: one output vector per
-// thread when the dense tiling is split (the host knows that split), and at
+// thread when the dense tiling is split (the host knows that split; with pixel
+// classes also where lists of every pixel would be), and at
 // least one per resident GEMM workgroup, which covers gather mode's split
 // (decided on the device, over at most half that many tiles) with a few
 // vectors per thread.  Each vector's loads are one chain of latency, so the
@@ -1181,12 +1182,11 @@ __global__ __launch_bounds__(256) void splitk_data_reduce_kernel(ParamsFor<UNIT>
 template <typename P>
 int data_reduce_blocks(const P& p)
 {
-    int64_t nvec = 0;
-    if (p.split > 1) {
-        const int bm = p.tile == 0 ? Tile<0>::BM : p.tile == 1 ? Tile<1>::BM : Tile<2>::BM;
-        const int bn = p.tile == 0 ? Tile<0>::BN : p.tile == 1 ? Tile<1>::BN : Tile<2>::BN;
-        nvec = (int64_t)data_split_tiles(p) * bn * (bm / 4);
-    }
+    int64_t tiles = p.split > 1 ? data_split_tiles(p) : 0;
+    if constexpr (std::is_same_v<P, DataParamsStrided>) tiles = std::max<int64_t>(tiles, p.list_tiles);
+    const int bm = p.tile == 0 ? Tile<0>::BM : p.tile == 1 ? Tile<1>::BM : Tile<2>::BM;
+    const int bn = p.tile == 0 ? Tile<0>::BN : p.tile == 1 ? Tile<1>::BN : Tile<2>::BN;
+    const int64_t nvec = tiles * bn * (bm / 4);
     return (int)std::max<int64_t>(p.nslots, (nvec + 255) / 256);
 }
 

@@ -103,6 +103,7 @@ constexpr int kDataTileSteps = 8;   // what starting and finishing a tile costs,
 struct DataParamsStrided : DataParams {
     int ncls;                // 0: every tap of every pixel
     int ptaps;               // pixel tiles that a tap reaches, the first of ptiles; the others are not split
+    int list_tiles;          // gather mode: tiles the reduction's grid is sized for at least
     int64_t cls_cost;        // steps of the class tiling, every tile kDataTileSteps on top
     // gather mode: the rows run per channel group, for the reduction and the
     // statistics: every pixel where the class tiling ran over dead ones too,

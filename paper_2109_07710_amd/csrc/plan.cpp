@@ -232,6 +232,8 @@ int plan_data(const cbw_conv_desc* d, bool masked, DataPlan* out, bool no_split,
     // and 25.1; C = 144: 28.2 and 34.7).
     if (p.nsteps == 1 && p.bm > 64 && p.ptiles * p.groups <= kDataSlots) p.ncls = 0;
     if (p.ncls > 0) {
+        const int all = p.groups * (int)((p.npix + p.bn - 1) / p.bn);
+        p.list_tiles = host_data_split(all, p.nsteps) > 1 ? all : 0;
         // full tiles: a tile's time hardly depends on its rows, and with
         // classes of different taps rounds of tiles say little (128 -> 256
         // channels, 56 x 56, N = 32: 35 us with 448 rows, 37 with 416, 39

@@ -43,6 +43,7 @@ struct DataPlan {
         int a = 0, b = 0, i0 = 0, j0 = 0, nh = 0, nw = 0, nr = 0, ns = 0, tile0 = 0;
         int64_t npix = 0;
     } cls[kDataMaxClasses];
+    int list_tiles = 0;     // classes: tiles of the lists at most, where they would be split (0: not)
     // Row-window kernel (data_rows_eligible): a workgroup per (column
     // segment, strip of rows_per_strip output rows), nbw 16-column blocks
     // per wave at most; it replaces the tiled GEMM and its compaction.
