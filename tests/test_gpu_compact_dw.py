@@ -119,3 +119,127 @@ def test_more_live_pixels_than_the_list_holds():
     assert -(-(-(-live // 64)) // nsplit) * 64 > 7168, "the case has to exceed the list"
     assert st.blocks_skipped == 0
     assert torch.equal(a, b)
+
+
+def _pack(desc, a):
+    bits = torch.zeros(cb.cbw_dy_mask_words(desc), dtype=torch.int32, device="cuda")
+    cb.cbw_nonzero_mask_pack(desc.dtype, a.numel(), a, bits)
+    return bits
+
+
+@pytest.mark.parametrize("form", ["x_mask", "x_values", "superset"])
+def test_compaction_beside_x_blocks(form):
+    """X-block skipping: a tile compacts where the live pixels of dY's footprint
+    (here also a strict superset of dY's non-zeros) fit half its blocks live in
+    both operands, and then runs every one of them.  Three channel tiles: X
+    live everywhere, in half the images (compacts too), in a few (the live
+    blocks are walked)."""
+    N, C, H, W, K, R, S = 24, 576, 20, 20, 256, 3, 3
+    print("\n[case] compacted dW beside X blocks, %s" % form, flush=True)
+    rng = np.random.default_rng([210907710, 94])
+    desc = cb.ConvDesc.make(N, C, H, W, K, R, S, 1, (1, 1))
+    xf = np.maximum(rng.standard_normal((N, H, W, C), dtype=np.float32), 0.0)
+    xf[N // 2:, :, :, 256:512] = 0.0
+    xf[4:, :, :, 512:] = 0.0
+    dyf = _dy(rng, N * H * W, K, (0.1 if form == "superset" else 0.2,))
+    foot = dyf.copy()
+    if form == "superset":
+        foot[rng.random(N * H * W) < 0.1, 7] = 1.0
+    x, dy = torch.from_numpy(xf).bfloat16().cuda(), torch.from_numpy(dyf).bfloat16().cuda()
+    bits = _pack(desc, torch.from_numpy(foot).bfloat16().cuda())
+    xm = None
+    if form == "x_mask":
+        xm = torch.zeros(cb.cbw_mask_words(desc), dtype=torch.int32, device="cuda")
+        cb.cbw_nonzero_mask_pack(desc.dtype, x.numel(), x, xm)
+    ws = cb.workspace(desc, cb.CBW_OP_BWD_WEIGHT)
+    a, b = (torch.full((K, R, S, C), float("nan"), device="cuda") for _ in range(2))
+    cb.conv_bwd_weight_sparse_x(desc, x, dy, xm, bits, a, ws)
+    stats, work = cb.cbw_read_stats(desc, cb.CBW_OP_BWD_WEIGHT, ws), cb.cbw_read_weight_work(desc, ws)
+    _, chunk, kw = cb.cbw_read_occupancy(desc, ws)
+    cb.conv_bwd_weight_sparse_x(desc, x, dy, xm, bits, b, ws, cb.CBW_FLAG_NO_SKIP)
+    torch.cuda.synchronize()
+    pix = foot.reshape(N, H, W, K).transpose(0, 3, 1, 2) != 0
+    live = oracle.weight_block_liveness(oracle.nhwc_to_nchw(x.float().cpu().numpy()) != 0, pix, (R, S), (1, 1), (1, 1),
+                                        chunk, kw, 256, 1).sum(axis=3).reshape(-1)   # per tile, in the work items' order
+    blocks = -(-int((foot != 0).any(axis=1).sum()) // chunk)
+    nsplit = work.shape[0]
+    assert -(-(-(-N * H * W // chunk)) // nsplit) >= 16
+    compacts = (2 * blocks <= live) & (live - blocks >= 4 * nsplit)
+    assert compacts.reshape(R * S, 3)[:, :2].all() and not compacts.reshape(R * S, 3)[:, 2].any()
+    assert np.array_equal(work.sum(axis=0), np.where(compacts, blocks, live))
+    assert stats.blocks_skipped == stats.blocks_total - int(work.sum())
+    ref, ab, nt = oracle.conv_bwd_weight(oracle.nhwc_to_nchw(x.double().cpu().numpy()),
+                                         dy.double().cpu().numpy().reshape(N, H, W, K).transpose(0, 3, 1, 2).copy(),
+                                         (R, S), (1, 1), (1, 1), with_bound=True)
+    check_values(oracle.krsc_to_kcrs(a.cpu().double().numpy()), ref, ab, nt, tol_for("bf16"), False, "compacted dW, X blocks")
+    check_dw_regrouped(a, b, stats.blocks_skipped, "compacted dW, X blocks, against no skipping")
+
+
+@pytest.mark.parametrize("flags", [0, cb.CBW_FLAG_SKIP_X_BLOCKS], ids=["dy", "x_blocks"])
+@pytest.mark.parametrize("act,filters", [("nhwc", "krsc"), ("nhwc", "kcrs"), ("nchw", "krsc"), ("nchw", "kcrs")])
+def test_compaction_in_the_combined_call(act, filters, flags):
+    """conv_bwd_sparse records the live pixels in its preparation launch: the
+    gradients are the separate calls' bit for bit and the same blocks run."""
+    N, C, H, W, K, R, S = 36, 256, 20, 20, 512, 3, 3
+    print("\n[case] compacted dW in the combined call, %s %s flags %d" % (act, filters, flags), flush=True)
+    rng = np.random.default_rng([210907710, 95])
+    desc = cb.ConvDesc.make(N, C, H, W, K, R, S, 1, (1, 1), w_layout=filters, act_layout=act)
+    xf = np.maximum(rng.standard_normal((N, H, W, C), dtype=np.float32), 0.0)
+    xf[rng.random((N, H, W)) < 0.5] = 0.0
+    xf[N - 2:] = 0.0   # whole windows of X dead
+    dyf = _dy(rng, N * H * W, K, (0.3, 0.05)).reshape(N, H, W, K)
+    x, dy = (torch.from_numpy(v).bfloat16() for v in (xf, dyf))
+    w = torch.from_numpy(rng.standard_normal((K, R, S, C), dtype=np.float32)).bfloat16()
+    if act == "nchw":
+        x, dy = (v.permute(0, 3, 1, 2).contiguous() for v in (x, dy))
+    if filters == "kcrs":
+        w = w.permute(0, 3, 1, 2).contiguous()
+    x, dy, w = x.cuda(), dy.cuda(), w.cuda()
+    bits = _pack(desc, dy)
+    xm = torch.zeros(cb.cbw_mask_words(desc), dtype=torch.int32, device="cuda")
+    cb.cbw_relu_mask_pack(desc, x, xm)
+    dx, sdx = (torch.full_like(x, float("nan")) for _ in range(2))
+    dw, sdw = (torch.full(w.shape, float("nan"), device="cuda") for _ in range(2))
+    wb, wd, ww = (cb.workspace(desc, op) for op in (cb.CBW_OP_BWD_BOTH, cb.CBW_OP_BWD_DATA_MASKED, cb.CBW_OP_BWD_WEIGHT))
+    cb.conv_bwd_sparse(desc, x, dy, w, xm, bits, dx, dw, wb, flags)
+    cb.conv_bwd_data_masked(desc, dy, w, xm, sdx, wd)
+    if flags:
+        cb.conv_bwd_weight_sparse_x(desc, x, dy, xm, bits, sdw, ww)
+    else:
+        cb.conv_bwd_weight_sparse(desc, x, dy, bits, sdw, ww)
+    both, weight = (cb.cbw_read_stats(desc, op, v) for op, v in ((cb.CBW_OP_BWD_BOTH, wb), (cb.CBW_OP_BWD_WEIGHT, ww)))
+    torch.cuda.synchronize()
+    assert torch.equal(dx.view(torch.int16), sdx.view(torch.int16))
+    assert torch.equal(dw.view(torch.int32), sdw.view(torch.int32))
+    work = cb.cbw_read_weight_work(desc, ww)
+    blocks = [-(-int((dyf[..., 256 * k:256 * k + 256] != 0).any(axis=3).sum()) // 64) for k in (0, 1)]
+    assert list(work.sum(axis=0)) == blocks * (work.shape[1] // 2)   # every tile compacts
+    assert both.blocks_skipped == weight.blocks_skipped == both.blocks_total - int(work.sum())
+
+
+def test_one_workspace_compacted_and_not():
+    """Calls that compact, walk live chunks, skip nothing and compact another
+    footprint, in turn over one workspace: each the result of its own."""
+    N, C, H, W, K, R, S = 36, 256, 20, 20, 512, 3, 3
+    print("\n[case] one workspace, compacted and not", flush=True)
+    rng = np.random.default_rng([210907710, 96])
+    desc = cb.ConvDesc.make(N, C, H, W, K, R, S, 1, (1, 1))
+    x = torch.from_numpy(np.maximum(rng.standard_normal((N, H, W, C), dtype=np.float32), 0.0)).bfloat16().cuda()
+    calls = []
+    for shares in ((0.1, 0.1), (1.0, 1.0), (0.7, 0.7), (0.02, 0.3), (0.0, 0.0), (0.1, 1.0)):
+        dyf = _dy(rng, N * H * W, K, shares)
+        if shares == (0.7, 0.7):
+            dyf[:N * H * W // 3] = 0.0   # dead chunks beside dense ones
+        dy = torch.from_numpy(dyf).bfloat16().cuda()
+        fresh = torch.full((K, R, S, C), float("nan"), device="cuda")
+        ws = cb.workspace(desc, cb.CBW_OP_BWD_WEIGHT)
+        cb.conv_bwd_weight_sparse(desc, x, dy, _pack(desc, dy), fresh, ws)
+        calls.append((dy, _pack(desc, dy), fresh, cb.cbw_read_stats(desc, cb.CBW_OP_BWD_WEIGHT, ws).blocks_skipped))
+    assert calls[1][3] == 0 and all(c[3] > 0 for i, c in enumerate(calls) if i != 1)
+    shared = cb.workspace(desc, cb.CBW_OP_BWD_WEIGHT)
+    for i in (0, 1, 2, 3, 4, 5, 1, 0, 2, 0, 4, 3):
+        dy, bits, fresh, skipped = calls[i]
+        dw = torch.full((K, R, S, C), float("nan"), device="cuda")
+        cb.conv_bwd_weight_sparse(desc, x, dy, bits, dw, shared)
+        assert cb.cbw_read_stats(desc, cb.CBW_OP_BWD_WEIGHT, shared).blocks_skipped == skipped
+        assert torch.equal(dw.view(torch.int32), fresh.view(torch.int32)), "call %d" % i
