@@ -90,6 +90,8 @@ inline int host_data_split(int T, int nsteps, int unsplit = 0)
 // the tile; the R*S taps go into as few groups as that allows, spread
 // evenly over them.
 int weight_tile_k_for(const cbw_conv_desc* d);
+// Splits of the fp32 weight gradient, `wgs` workgroups each.
+int f32_weight_splits(const cbw_conv_desc* d, int64_t wgs, int nchunks, int max_split);
 int weight_taps_per_group(const cbw_conv_desc* d);
 
 struct WeightPlan {

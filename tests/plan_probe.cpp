@@ -23,4 +23,22 @@ int probe_data_plan(const cbw_conv_desc* d, int masked, int64_t* out)
     return st;
 }
 
+// workgroups a split, chunks, splits
+int probe_f32_weight_plan(const cbw_conv_desc* d, int64_t* out)
+{
+    cbw::WeightPlan p;
+    const int st = cbw::plan_weight(d, &p, true);
+    out[0] = (int64_t)p.tgroups * p.ctiles * p.ktiles * p.subc * p.subk;
+    out[1] = p.nchunks;
+    out[2] = p.nsplit;
+    return st;
+}
+
+// fills the splits of `n` cases of (workgroups, chunks, limit)
+void probe_f32_weight_splits(const cbw_conv_desc* d, int n, const int64_t* cases, int32_t* splits)
+{
+    for (int i = 0; i < n; ++i)
+        splits[i] = cbw::f32_weight_splits(d, cases[3 * i], (int)cases[3 * i + 1], (int)cases[3 * i + 2]);
+}
+
 }  // extern "C"

@@ -2,7 +2,9 @@
 (tests/plan_probe.cpp): index arithmetic that a kernel shares with them, and
 plans at the edges of their ranges."""
 import ctypes
+import math
 import os
+import random
 import subprocess
 
 import pytest
@@ -79,3 +81,43 @@ def test_tap_free_tiles_are_not_split(P, layer, dtype):
         most = min(16, steps, (256 - free) // taps)
         cost = lambda n: 1.1 * -(-steps // n) + (6.0 + rows * bm * 4e-6 * taps * n / 10.0 if n > 1 else 0.0)  # noqa: E731
         assert split == (most if dtype == "f32" else min(range(1, most + 1), key=cost))
+
+
+def _cheapest_split(part, wgs, nchunks, max_split):
+    """The fp32 weight gradient's cost model over every count of splits."""
+    best, least = 1, None
+    for ns in range(1, min(max_split, 768) + 1):
+        per = -(-nchunks // ns)
+        if -(-nchunks // per) != ns:
+            continue
+        w = -(-wgs * ns // 256)
+        cost = 1.9 * w * ((per + 3) // 4) + 3.0 * ((w + 2) // 3) + part * ns
+        if least is None or cost < least:
+            best, least = ns, cost
+    return best
+
+
+def test_f32_weight_splits_are_the_cheapest(P):
+    """The planner skips counts that cannot be the cheapest: its choice is the
+    one of trying them all, for few and many workgroups, chunks and bytes."""
+    rng = random.Random(5)
+    log = lambda lo, hi: int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))  # noqa: E731
+    for C, K, R in ((4, 4, 1), (16, 16, 3), (64, 128, 3), (512, 512, 3), (2048, 1024, 1)):
+        d = cb.ConvDesc.make(1, C, 8, 8, K, R, R, 1, (R // 2, R // 2), dtype="f32")
+        cases = [(log(1, 3000), n, max(1, n // 4)) for n in [1, 2, 3, 4, 5, 7, 8, 9, 63, 64, 65] + [log(1, 60000) for _ in range(300)]]
+        flat = (ctypes.c_int64 * (3 * len(cases)))(*[v for c in cases for v in c])
+        got = (ctypes.c_int32 * len(cases))()
+        P.probe_f32_weight_splits(ctypes.byref(d), len(cases), flat, got)
+        for c, ns in zip(cases, got):
+            assert ns == _cheapest_split(K * R * R * C * 8 / 4e6, *c), (C, K, R, c)
+
+
+@pytest.mark.parametrize("layer", [(2, 16, 16, 16, 3), (16, 128, 28, 128, 3), (8, 256, 28, 256, 3), (4, 64, 112, 64, 3),
+                                   (100, 8, 63, 32, 1)], ids=str)
+def test_f32_weight_plan(P, layer):
+    N, C, H, K, R = layer
+    d = cb.ConvDesc.make(N, C, H, H, K, R, R, 1, (R // 2, R // 2), dtype="f32")
+    out = (ctypes.c_int64 * 3)()
+    assert P.probe_f32_weight_plan(ctypes.byref(d), out) == cb.CBW_OK
+    wgs, nchunks, nsplit = out
+    assert nsplit == _cheapest_split(K * R * R * C * 8 / 4e6, wgs, nchunks, max(1, nchunks // 4))
