@@ -103,7 +103,10 @@ typedef struct {
     int64_t rows_total;      /* GEMM rows (pixel x channel-group) the dense path would compute */
     int64_t rows_live;       /* rows actually computed                                        */
     int64_t blocks_total;    /* dW GEMM blocks: pixel chunk x k tile x tap group x channel tile */
-    int64_t blocks_skipped;  /* dW blocks skipped (dY, or with the _x variant X, all zero)     */
+    int64_t blocks_skipped;  /* dW blocks not executed: dY (with the _x variant or X) all zero;
+                                where a tile ran over compacted pixels (see
+                                conv_bwd_weight_sparse), its chunks less the blocks of live
+                                pixels it ran                                              */
 } cbw_stats;
 
 /* Host-only inspection of the data-gradient tiling that conv_bwd_data and
@@ -114,7 +117,11 @@ typedef struct {
  * resident tile per CU (tiles / CUs rounded up, times the rows); the full
  * capacity whenever the tiles are few enough for the reduction to be split.
  * The skipping masked call makes the same choice on the device from the live
- * pixel counts.  Any output pointer may be NULL.  Returns CBW_OK or the
+ * pixel counts.  With a stride (of at most 16 residues, stride_h * stride_w;
+ * not where one round of tiles of over 64 channels takes one step each) the tiles always cover the full capacity, each of pixels that the same
+ * filter taps reach, every pixel's; the skipping call runs these tiles too
+ * unless tiles over the live pixels alone, which walk every tap, take fewer
+ * steps.  Any output pointer may be NULL.  Returns CBW_OK or the
  * descriptor's validation status. */
 int cbw_data_tiling(const cbw_conv_desc* desc, int32_t* channels, int32_t* capacity, int32_t* rows);
 
@@ -202,8 +209,14 @@ int conv_fwd_relu_mask(const cbw_conv_desc* desc, const void* X, const void* W, 
  * entirely zero are skipped; the skipped products are exactly zero.  dy_mask
  * (nullable) is a packed dY footprint (cbw_nonzero_mask_pack or the next
  * layer's ReLU bitmap, any superset of dY's non-zeros; 16-byte aligned);
- * when NULL the occupancy is read from dY itself.  The result is deterministic: partial
- * sums are reduced in a fixed order.  dW is fully overwritten.
+ * when NULL the occupancy is read from dY itself.  bf16 with dy_mask and 16
+ * pixel chunks or more per split: where whole pixels of a k tile are dead (no
+ * bit of its output channels set) so that its live pixels fit half as many
+ * 64-pixel blocks as are live, saving four blocks a split on average, the
+ * tile runs blocks of live pixels instead of its live chunks (X's zeros
+ * count in that comparison only); the products left out are zero as well.  The
+ * result is deterministic: partial sums are reduced in a fixed order.  dW is
+ * fully overwritten.
  * Workspace: cbw_workspace_size(desc, CBW_OP_BWD_WEIGHT). */
 int conv_bwd_weight_sparse(const cbw_conv_desc* desc, const void* X, const void* dY,
                            const uint32_t* dy_mask, float* dW,
@@ -286,7 +299,9 @@ int cbw_read_pixel_counts(const cbw_conv_desc* desc, const void* workspace, size
  * number of blocks each work item executed, in item order z*ntiles + tile
  * (split z of tile ((tap group * channel tiles + channel tile) * k tiles +
  * k tile)).  With skipping, the live blocks of every tile are shared out in
- * equal ceil(live / nsplit) parts (work redistribution, Sec. IV-F).
+ * equal ceil(live / nsplit) parts (work redistribution, Sec. IV-F): its live
+ * chunks, or where they are fewer the blocks of its compacted pixels (see
+ * conv_bwd_weight_sparse).
  * `work` (nullable) receives nsplit*ntiles int32; waits for `stream`. */
 int cbw_read_weight_work(const cbw_conv_desc* desc, const void* workspace, size_t workspace_bytes, int32_t* work,
                          int32_t* nsplit, int32_t* ntiles, void* stream);
@@ -310,7 +325,9 @@ int cbw_read_stats(const cbw_conv_desc* desc, int op, const void* workspace, siz
  * CBW_FLAG_NO_SKIP, copies the block occupancy map occ[chunk][ktile] (uint8,
  * 1 = dY has a non-zero in that block) to `occ` (capacity *nchunks x
  * *ktiles, both returned; chunk = *chunk_pixels pixels of dY in N,P,Q order,
- * ktile = *ktile_width output channels).  `occ` may be NULL to query sizes. */
+ * ktile = *ktile_width output channels).  `occ` may be NULL to query sizes.
+ * The map tells which blocks hold a non-zero, not how many were executed: a
+ * tile over compacted pixels runs fewer (cbw_read_weight_work). */
 int cbw_read_live_lists(const cbw_conv_desc* desc, const void* workspace, size_t workspace_bytes, int group,
                         int32_t* pixels, int32_t* count, int32_t* group_width, void* stream);
 int cbw_read_occupancy(const cbw_conv_desc* desc, const void* workspace, size_t workspace_bytes, uint8_t* occ,

@@ -200,13 +200,4 @@ __device__ __forceinline__ int xcd_remap(int b, int nb)
     return xcd * per + (xcd < rem ? xcd : rem) + j;
 }
 
-// Swizzle of a 16-byte chunk inside a 256-byte LDS row (16 chunks).  Chosen
-// so that sixteen consecutive rows read at one logical chunk, and rows
-// 8c + j for c = 0..15 written at one logical chunk, fall on sixteen
-// different chunk positions.
-__device__ __forceinline__ int swz16(int row)
-{
-    return (row & 15) ^ ((row >> 4) & 7);
-}
-
 }  // namespace cbw

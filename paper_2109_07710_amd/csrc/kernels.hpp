@@ -186,7 +186,7 @@ struct WeightParams {
     uint32_t x_bytes, dy_bytes;
     FastDiv div_q, div_p;    // pixel -> (n, p, q)
     // this call's number: header[kDeadWord] == gen when the occupancy pass
-    // found a dead block (bf16 kernels; see OccParams)
+    // found a dead block (the kernels over pixel chunks; see OccParams)
     uint32_t gen;
     const uint64_t* pmask;   // [ktiles][nchunks] live pixels of each block, or null (see OccParams)
 };

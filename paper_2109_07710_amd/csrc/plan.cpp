@@ -330,8 +330,8 @@ bool weight_rows_eligible(const cbw_conv_desc* d)
 // finishing takes about 3 us per three; every split writes and reads back
 // the whole gradient at about 4 TB/s.  The cheapest count by that model:
 // as many splits as fill the CUs once left them idle where the quotient is
-// small (256 -> 256 channels, 28 x 28, N = 8: 144 workgroups a split, one
-// split 128 us, five 94, with workgroups of eight waves).  Only the counts at
+// small (256 -> 256 channels, 28 x 28, N = 8: 144 workgroups a split, five
+// splits).  Only the counts at
 // which a CU's share (w) or a wave's chunks (g) change are tried, and none
 // past the point where the partials and starts alone cost more than the
 // difference to perfectly shared work: the same choice as by trying all of

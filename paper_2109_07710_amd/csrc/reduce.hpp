@@ -1,6 +1,5 @@
 // Split-K reduction of the weight gradient (device body, shared by its own
-// launch, the combined reduction launch and the tail workgroups of the
-// data-gradient GEMM launch).
+// launch and the tail workgroups of the data-gradient GEMM launch).
 #pragma once
 
 #include "common.hpp"
