@@ -127,7 +127,7 @@ void data_gemm_params(const cbw_conv_desc* desc, const DataPlan& plan, const voi
         p.counts = at<int32_t>(ws, plan.counts);
         p.dead_flags = cp.dead_flags;
         p.rows_run = at<int32_t>(ws, plan.header) + kRowsRunWord;
-        p.list_tiles = plan.list_tiles;
+        p.list_tiles = no_split ? 0 : plan.list_tiles;
     }
     *out = p;
     *cpo = cp;
