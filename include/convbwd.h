@@ -118,11 +118,12 @@ typedef struct {
  * capacity whenever the tiles are few enough for the reduction to be split.
  * The skipping masked call makes the same choice on the device from the live
  * pixel counts.  With a stride (of at most 16 residues, stride_h * stride_w;
- * not where one round of tiles of over 64 channels takes one step each) the tiles always cover the full capacity, each of pixels that the same
- * filter taps reach, every pixel's; the skipping call runs these tiles too
- * unless tiles over the live pixels alone, which walk every tap, take fewer
- * steps.  Any output pointer may be NULL.  Returns CBW_OK or the
- * descriptor's validation status. */
+ * not where one round of tiles of over 64 channels takes one step each) the
+ * tiles always cover the full capacity, each of pixels that the same filter
+ * taps reach, every pixel's; the skipping call runs these tiles too unless
+ * tiles over the live pixels alone, which walk every tap, take fewer steps.
+ * Any output pointer may be NULL.  Returns CBW_OK or the descriptor's
+ * validation status. */
 int cbw_data_tiling(const cbw_conv_desc* desc, int32_t* channels, int32_t* capacity, int32_t* rows);
 
 /* Human-readable name of a cbw_status value (static storage). */
