@@ -266,10 +266,10 @@ __device__ __forceinline__ int class_pixel(const DataParamsStrided& p, const Dat
 // by the steps of both (`listed` tiles of the lists).  Element-wise
 // footprints of narrow layers have a few dead pixels: 8 -> 280 channels,
 // 3x3 stride 2, 199x199, N = 3, 64% of the elements live: both gradients
-// 94.6 us over the lists, 74.8 over the classes.  The tiles of the classes are
-// those the speculation started; no list is built (building them for the
-// readers, who take the preparation launch's bits, and starting again took
-// 5 to 7 us: 128 -> 256, 125x125, N = 4, 65% of the pixels live: 88.7 -> 82.3).
+// 94.6 us over the lists, 74.8 over the classes.  No list is built then
+// (building them for the readers, who take the preparation launch's bits, and
+// starting the item a second time took 5 to 7 us: 128 -> 256, 125x125, N = 4,
+// 65% of the pixels live: 88.7 -> 82.3).
 __device__ __forceinline__ bool classes_win(const DataParamsStrided& p, int listed, int nsteps)
 {
     return p.ncls > 0 && (int64_t)listed * (nsteps + kDataTileSteps) > p.cls_cost;
@@ -334,7 +334,7 @@ __global__ __launch_bounds__(Tile<TI>::NT) void bwd_data_kernel(ParamsFor<UNIT> 
     // chunks) is split S ways and the partial tiles are summed afterwards
     // (splitk_data_reduce_kernel); every workgroup derives the same S.
     //
-    // Gather mode speculates: it first takes the dense mode's tiles, which
+    // Gather mode (unit strides) speculates: it first takes the dense mode's tiles, which
     // are exactly its own when every pixel of every group is live (the usual
     // case for element-wise footprints), and issues their first copies at
     // once; when the preparation launch flagged a dead pixel, the copies are
@@ -664,19 +664,30 @@ __global__ __launch_bounds__(Tile<TI>::NT) void bwd_data_kernel(ParamsFor<UNIT> 
     // flag), issued behind step 0's copies and complete with them, so the
     // usual case (every pixel live) pays nothing: a scalar read loop ahead of
     // the copies waited for each load before the first copy went out (1.8 us
-    // per launch).
-    map_item(true);
-    if (active) start_item();
+    // per launch).  With strides the load goes out first and the item is started
+    // once: its latency passes under the item's arithmetic (layers with every
+    // pixel live: the same within 0.3%), no copy is dropped, and one start in
+    // place of two leaves the kernel without scalar spills.  192 -> 32 channels,
+    // 3x3 stride 2, 124x124, N = 2, 32% of the pixels live: both gradients 65.1 ->
+    // 61.9 us (62.7 before the classes); 24 -> 40, 1x1, 79x79, N = 73: 65.8 ->
+    // 57.5 (68.1).
+    constexpr bool FLAG_FIRST = MODE == MODE_GATHER && !UNIT;
     uint32_t dflag = 0;
-    if (MODE == MODE_GATHER) {
+    auto load_flag = [&]() {
         const __amdgpu_buffer_rsrc_t rs_f = make_rsrc(p.dead_flags, (uint32_t)p.ctiles * 4u);
         dflag = __builtin_amdgcn_raw_buffer_load_b32(rs_f, lane < p.ctiles ? 4u * lane : kOOB, 0, 0);
+    };
+    if constexpr (FLAG_FIRST) load_flag();
+    map_item(true);
+    if constexpr (!FLAG_FIRST) {
+        if (active) start_item();
+        if (MODE == MODE_GATHER) load_flag();
+        wait_vmem();
+        __syncthreads();
     }
-    wait_vmem();
-    __syncthreads();
     const bool anydead = MODE == MODE_GATHER && __ballot(dflag != 0u) != 0ull;
     if (MODE == MODE_GATHER && anydead) {
-        // speculation failed (the copies have landed): every group's live
+        // not the dense tiles (unit strides: the speculative copies have landed): every group's live
         // total from the block counts (workgroup 0 also stores them for the
         // reduction kernel and the readers), then the tiles over the live lists
         for (int g = 0; g < p.ctiles; ++g) {
@@ -703,7 +714,7 @@ __global__ __launch_bounds__(Tile<TI>::NT) void bwd_data_kernel(ParamsFor<UNIT> 
         __syncthreads();
         // (a stale flag with every pixel live keeps the dense tiling, which the
         // split reduction takes for it, and so do pixel classes that are cheaper
-        // than the lists: their copies are the speculative ones)
+        // than the lists)
         bool all = true;
         for (int g = 0; g < p.ctiles; ++g) all &= gtot_s[g] == p.npix;
         if constexpr (MODE == MODE_GATHER && !UNIT) {
@@ -714,13 +725,20 @@ __global__ __launch_bounds__(Tile<TI>::NT) void bwd_data_kernel(ParamsFor<UNIT> 
         }
         if (!__builtin_amdgcn_readfirstlane((int)all)) {
             map_item(false);
-            if (active) start_item();
-            wait_vmem();
-            __syncthreads();
+            if constexpr (!FLAG_FIRST) {
+                if (active) start_item();
+                wait_vmem();
+                __syncthreads();
+            }
         }
     } else if (MODE == MODE_GATHER && blockIdx.x == 0 && tid < p.ctiles) {
         p.counts[tid] = p.npix;   // every pixel live
         if constexpr (!UNIT) p.rows_run[tid] = p.npix;
+    }
+    if constexpr (FLAG_FIRST) {
+        if (active) start_item();
+        wait_vmem();
+        __syncthreads();
     }
     if (!active) return;   // uniform across the workgroup
     auto main_loop = [&](auto nb_tag) {
