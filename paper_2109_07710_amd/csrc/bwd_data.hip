@@ -723,13 +723,15 @@ __global__ __launch_bounds__(Tile<TI>::NT) void bwd_data_kernel(ParamsFor<UNIT> 
             all = all || classes_win(p, tiles, nsteps);
             if (blockIdx.x == 0 && tid < p.ctiles) p.rows_run[tid] = all ? p.npix : gtot_s[tid];
         }
-        if (!__builtin_amdgcn_readfirstlane((int)all)) {
-            map_item(false);
-            if constexpr (!FLAG_FIRST) {
-                if (active) start_item();
-                wait_vmem();
-                __syncthreads();
-            }
+        if constexpr (FLAG_FIRST) {
+            if (!__builtin_amdgcn_readfirstlane((int)all)) map_item(false);
+        } else {
+            // (skipping the second start where every pixel is live, a stale
+            // flag alone, cost the usual case up to 0.6%)
+            map_item(__builtin_amdgcn_readfirstlane((int)all) != 0);
+            if (active) start_item();
+            wait_vmem();
+            __syncthreads();
         }
     } else if (MODE == MODE_GATHER && blockIdx.x == 0 && tid < p.ctiles) {
         p.counts[tid] = p.npix;   // every pixel live
