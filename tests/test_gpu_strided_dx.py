@@ -107,3 +107,36 @@ def test_strided_dx(case, dead):
         if k != "dense":   # killed outputs are the +0.0 bit pattern
             bits = g.view(torch.int16 if dt == "bf16" else torch.int32).cpu().numpy()
             assert not (oracle.nchw_to_nhwc(~mask) & (bits != 0)).any()
+
+
+@pytest.mark.parametrize("fill", [0, -1])
+def test_one_workspace_live_and_dead(fill):
+    """Calls with every pixel live, few dead (the classes), most dead (the lists)
+    and the other way round over one workspace, whatever it held: each the
+    result of a workspace of its own (a dead-pixel flag may be stale)."""
+    N, C, H, W, K, R, S = 4, 256, 40, 38, 128, 3, 3
+    print("\n[case] strided dX, one workspace filled with %d" % fill, flush=True)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(9)
+    desc = cb.ConvDesc.make(N, C, H, W, K, R, S, 2, (1, 1))
+    dy = torch.randn((N, desc.P, desc.Q, K), generator=g, device="cuda").bfloat16()
+    w = torch.randn((K, R, S, C), generator=g, device="cuda").bfloat16()
+    calls = []
+    for dead in (0.0, 0.01, 0.95):
+        x = torch.randn((N, H, W, C), generator=g, device="cuda").abs_() + 0.1
+        x[torch.rand((N, H, W), generator=g, device="cuda") < dead] = 0.0
+        xm = torch.zeros(cb.cbw_mask_words(desc), dtype=torch.int32, device="cuda")
+        cb.cbw_relu_mask_pack(desc, x.bfloat16(), xm)
+        dx = torch.full((N, H, W, C), float("nan"), dtype=torch.bfloat16, device="cuda")
+        ws = cb.workspace(desc, cb.CBW_OP_BWD_DATA_MASKED).zero_()
+        cb.conv_bwd_data_masked(desc, dy, w, xm, dx, ws)
+        calls.append((xm, dx, cb.cbw_read_stats(desc, cb.CBW_OP_BWD_DATA_MASKED, ws).rows_live))
+    assert calls[0][2] == calls[1][2] == N * H * W > 5 * calls[2][2]
+    ws = cb.workspace(desc, cb.CBW_OP_BWD_DATA_MASKED)
+    ws.fill_(255 if fill else 0) if ws.dtype == torch.uint8 else ws.fill_(fill)
+    for i in (0, 2, 1, 0, 1, 2, 2, 0):
+        xm, ref, rows = calls[i]
+        dx = torch.full_like(ref, float("nan"))
+        cb.conv_bwd_data_masked(desc, dy, w, xm, dx, ws)
+        assert cb.cbw_read_stats(desc, cb.CBW_OP_BWD_DATA_MASKED, ws).rows_live == rows
+        assert torch.equal(dx.view(torch.int16), ref.view(torch.int16)), "call %d" % i
